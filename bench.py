@@ -474,7 +474,7 @@ def run_map(args, torch, api, synth):
                        "n": n, "d": d, "replicas": R, "round_trips": steps, "precision": "f32"},
             "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                          "frac": achieved / PEAK_BF16_TFLOPS, "traffic": None,
-                         "kernel": "k_integrate_resident<7, 3, 3, 1, true>", "kernel_ms": kms}}
+                         "kernel": "k_integrate_team<3, 3, 1, 4, 2, false, true> (plane layout)", "kernel_ms": kms}}
 
 
 def run_sparse(args, torch, api, synth):

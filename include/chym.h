@@ -142,8 +142,8 @@ const char *chym_last_error(void);
  * steps - 1.  Splitting a run into calls with consecutive start_step gives
  * bit-identical results to one call.
  *
- * Two integrators, chosen by size, give identical results for the same
- * problem: a register-resident one (no workspace) up to n = 192 (d = 1),
+ * Three integrators, chosen by size and replica count, give identical results
+ * for the same problem: a register-resident one (no workspace) up to n = 192 (d = 1),
  * 144/160 (d = 2, float32/bf16 form), 128 (d = 3), 112 (d = 4), or less
  * for float J in the float32 form; and a streamed-J one for larger n, up to
  * n = 1024 in both forms, which needs a caller workspace (chym_integrate_ws).
@@ -151,7 +151,11 @@ const char *chym_last_error(void);
  * ceil(n/32) * d * terms KiB (terms = 1 in the bf16 form, 3 in the float32
  * form), in LDS; where that exceeds 159 KiB (the float32 form beyond n = 832,
  * 544, 416 for d = 2, 3, 4) it holds one component at a time and reads J d
- * times per step, with the same results.  chym_integrate returns
+ * times per step, with the same results.  Up to n = 256, launches whose
+ * replicas do not fill the chip on these (and most beyond the
+ * register-resident sizes) run on the team integrator, which spreads a
+ * problem's rows over the wavefronts of a block; the sizes that need a
+ * workspace need it all the same.  chym_integrate returns
  * CHYM_EUNSUPPORTED where a workspace is needed. */
 int chym_integrate(const chym_problem *prob, const chym_run *run, chym_stream_t stream);
 

@@ -35,21 +35,25 @@ int hip_fail(hipError_t e, const char *what) {
 }
 
 // The kernels are built for gfx950 only: refuse any other device up front.
-int check_device() {
+// cus, if given, receives the current device's compute units.
+int check_device(int *cus = nullptr) {
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail(CHYM_ENODEV, "no HIP device: %s", hipGetErrorString(e));
     static std::mutex mu;
     static int ok[64];  // 0 unknown, 1 gfx950, -1 other
+    static int units[64];
     if (dev < 0 || dev >= 64) return fail(CHYM_ENODEV, "device index %d out of range", dev);
     std::lock_guard<std::mutex> lk(mu);
     if (ok[dev] == 0) {
         hipDeviceProp_t prop;
         e = hipGetDeviceProperties(&prop, dev);
         if (e != hipSuccess) return hip_fail(e, "hipGetDeviceProperties");
+        units[dev] = prop.multiProcessorCount;
         ok[dev] = strncmp(prop.gcnArchName, "gfx950", 6) == 0 ? 1 : -1;
     }
     if (ok[dev] != 1) return fail(CHYM_ENODEV, "device %d is not gfx950", dev);
+    if (cus) *cus = units[dev];
     return CHYM_OK;
 }
 
@@ -167,12 +171,19 @@ int integrate_impl(const chym_problem *prob, const chym_run *run, hipStream_t st
         if ((uintptr_t)ws % 256) return fail(CHYM_EINVAL, "workspace must be 256-byte aligned");
     }
     if (run->steps == 0) return CHYM_OK;
-    rc = check_device();
+    int cus = 0;
+    rc = check_device(&cus);
     if (rc) return rc;
     const chym::IntegArgs a = make_args(prob, run);
     if (prob->j_dtype == CHYM_J_ELL) {
         hipError_t e = chym::launch_integrate_ell(a, stream);
         if (e != hipSuccess) return hip_fail(e, "sparse integrate launch");
+        return CHYM_OK;
+    }
+    const int layout = chym::team_layout(v.tiles, prob->d, v.xs, v.js, run->r, false, cus);
+    if (layout != chym::kTeamNone) {
+        hipError_t e = chym::launch_integrate_team(layout, v.tiles, prob->d, v.xs, v.js, false, a, stream);
+        if (e != hipSuccess) return hip_fail(e, "integrate launch");
         return CHYM_OK;
     }
     if (v.slab) {
@@ -853,12 +864,12 @@ int chym_map_integrate(const chym_map_problem *m, const chym_run *run, chym_stre
     int rc = map_setup(m, run, &t);
     if (rc) return rc;
     if (run->steps == 0) return CHYM_OK;
-    rc = check_device();
+    int cus = 0;
+    rc = check_device(&cus);
     if (rc) return rc;
-    bool supported = false;
-    hipError_t e = chym::launch_integrate_map(t.tiles, m->d, t.xs, default_waves_per_block(), t.a,
-                                              (hipStream_t)stream, &supported);
-    if (!supported) return fail(CHYM_EUNSUPPORTED, "no map variant for n = %d, d = %d", m->n, m->d);
+    const int layout = chym::team_layout(t.tiles, m->d, t.xs, 1, run->r, true, cus);
+    if (layout == chym::kTeamNone) return fail(CHYM_EUNSUPPORTED, "no map variant for n = %d, d = %d", m->n, m->d);
+    hipError_t e = chym::launch_integrate_team(layout, t.tiles, m->d, t.xs, 1, true, t.a, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "map integrate launch");
     return CHYM_OK;
 }

@@ -119,9 +119,7 @@ hipError_t launch_integrate(int tiles, int d, int xs, int js, int waves_per_bloc
 // tiles (the medium's gain per amplitude needs registers the largest
 // register-resident shapes do not have).
 constexpr int kMapMaxTiles = 7;
-hipError_t launch_integrate_map(int tiles, int d, int xs, int waves_per_block, const IntegArgs &a,
-                                hipStream_t stream, bool *supported);
-// Many map problems of one variant: a persistent grid of 256-thread blocks
+// Many map problems of one variant (register-resident kernels): a persistent grid of 256-thread blocks
 // whose wavefronts pop items (task, 16-replica group) from *counter (zero at
 // launch) until n_items are taken.
 bool map_variant_exists(int tiles, int d, int xs);
@@ -129,6 +127,15 @@ hipError_t map_persistent_occupancy(int tiles, int d, int xs, int *blocks_per_cu
 hipError_t launch_integrate_map_persistent(int tiles, int d, int xs, int blocks, const IntegArgs *tasks,
                                            const int2 *items, int n_items, int *counter, hipStream_t stream);
 bool integrate_variant_exists(int tiles, int d, int xs, int js);
+// Team integrator (a problem's row tiles spread over the wavefronts of a
+// block): the layout to take for r replicas on a GPU of cus compute units, or
+// kTeamNone where another integrator is faster; and its launch.
+constexpr int kTeamNone = 0;
+constexpr int kTeamPack = 1;   // 16 columns per block
+constexpr int kTeamPlane = 2;  // 16 replicas x d planes per block
+int team_layout(int tiles, int d, int xs, int js, int64_t r, bool map, int cus);
+hipError_t launch_integrate_team(int layout, int tiles, int d, int xs, int js, bool map, const IntegArgs &a,
+                                 hipStream_t stream);
 // Persistent kernel kinds: J gathered into each wavefront's registers, work
 // items of 16 replicas; or J staged in LDS per block, work items of
 // 16 * waves_per_block replicas.

@@ -1,5 +1,6 @@
 // Host-side dispatch of the register-resident integrator variants.
 #include "integrate_slab.h"
+#include "integrate_team.h"
 
 namespace chym {
 
@@ -13,7 +14,7 @@ static KernelFn lookup(int tiles, int d, int xs, int js) {
     CHYM_PICK(3, 3, 1) CHYM_PICK(3, 1, 1) CHYM_PICK(3, 3, 3)
     CHYM_PICK(4, 3, 1) CHYM_PICK(4, 1, 1) CHYM_PICK(4, 3, 3)
 #undef CHYM_PICK
-    return KernelSet{nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr};
+    return KernelSet{nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
 }
 
 int resident_tile_limit(int d, int xs, int js) {
@@ -219,6 +220,79 @@ hipError_t launch_integrate_slab_persistent(int tiles, int d, int xs, int js, in
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------ team kernels
+static TeamFn lookup_team(int tiles, int d, int xs, int js, bool pack, bool map) {
+    if (tiles < 1 || tiles > kTeamMaxTiles) return nullptr;
+    switch (d) {
+        case 1: return lookup_team_1(tiles, xs, js, pack, map);
+        case 2: return lookup_team_2(tiles, xs, js, pack, map);
+        case 3: return lookup_team_3(tiles, xs, js, pack, map);
+        case 4: return lookup_team_4(tiles, xs, js, pack, map);
+        default: return nullptr;
+    }
+}
+
+// Which integrator for r replicas.  Measured per step (us), +-1 couplings,
+// 256 CUs; "wave" is one wavefront per 16 replicas (the register-resident
+// kernel, 1024 SIMDs hold 16384 replicas), "slab" the streamed-J kernel:
+//   N = 100, D = 3, f32    16 replicas: packed 0.52, plane 1.24, wave 3.18
+//                          2048: 0.88, 1.33, 3.25    8192: 2.8, 2.1, 3.3
+//                          16384: 5.3, 4.1, 3.7      20000: 6.8, 5.2, 6.8
+//   N = 100, D = 2, f32    2048: 0.54, 0.97, 2.38    16384: 2.50, 2.69, 2.54
+//   N = 100, D = 4, f32    2048: 0.93, 1.66, 4.23    8192: 2.96, 3.43, 4.37
+//   N = 200, D = 3, bf16   1024: packed 0.63, plane 1.09, slab 1.44
+//                          20000: 11.6, 6.1, 8.2
+// Packed blocks have the shortest step, and are the fastest up to two of them
+// on a CU (four with two chunks, eight with one, and twice as many for the
+// map, whose steps hold more vector work).  Beyond that the plane layout is
+// faster where the packed one idles a column (D = 3) or where the quad sums
+// weigh more than the operand exchange (bf16); otherwise packed blocks stay
+// level with it.  Against one wavefront per 16 replicas both lose once those
+// fill the SIMDs: the wave's time goes up in steps of 16384 replicas, the
+// team's in proportion, so the line is drawn at 0.9 of a full step (0.7 with
+// three wavefronts on four SIMDs).  The map takes the team at every size: the
+// medium's gain is vector work, which one wavefront per SIMD cannot overlap
+// with its products (N = 100, D = 3, 65536 replicas: 28.2 us a step, plane
+// 23.4).  Against the streamed-J kernel both layouts win at every replica
+// count, except where no plane layout is built (its operand does not fit LDS
+// twice: float32 at D = 4 beyond 12 tiles) and J is one term: there packed
+// blocks are 5-10% slower beyond two to a CU.
+int team_layout(int tiles, int d, int xs, int js, int64_t r, bool map, int cus) {
+    if (!lookup_team(tiles, d, xs, js, true, map)) return kTeamNone;
+    const int nc = (tiles + 1) / 2;
+    const bool wave = map ? tiles <= kMapMaxTiles : tiles <= resident_tile_limit(d, xs, js);
+    if (nc == 1 && d == 1 && !map) return kTeamNone;  // the same work in the same single wavefront
+    if (wave && !map && nc > 1) {
+        const int64_t full = (int64_t)4 * cus * 16;
+        const int64_t steps = (r + full - 1) / full;
+        if (10 * r > (nc == 3 ? 7 : 9) * steps * full) return kTeamNone;
+    }
+    const bool plane = lookup_team(tiles, d, xs, js, false, map) != nullptr;
+    const int rp = team_replicas(d, true);
+    const int64_t per_cu = ((r + rp - 1) / rp + cus - 1) / cus;  // packed blocks
+    if (per_cu <= (nc == 1 ? 8 : nc == 2 ? 4 : 2) * (map ? 2 : 1)) return kTeamPack;
+    if (!wave && !plane && d > 1 && js == 1) return kTeamNone;
+    return plane && (nc == 1 || d == 3 || xs == 1) ? kTeamPlane : kTeamPack;
+}
+
+hipError_t launch_integrate_team(int layout, int tiles, int d, int xs, int js, bool map, const IntegArgs &a,
+                                 hipStream_t stream) {
+    const bool pack = layout == kTeamPack;
+    TeamFn fn = lookup_team(tiles, d, xs, js, pack, map);
+    if (!fn) return hipErrorInvalidDeviceFunction;
+    const int nc = (tiles + 1) / 2;
+    const int rb = team_replicas(d, pack);
+    const size_t lds = team_lds_bytes(nc, d, xs, pack);
+    if (lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(fn, dim3((a.r + rb - 1) / rb), dim3(64 * team_waves(nc, team_tiles(tiles, xs, pack))), lds,
+                       stream, a);
+    return hipGetLastError();
+}
+
 // Synthetic problem for timing runs: J = +-1 by a hash of (p, q) (symmetric,
 // zero diagonal), pump 1.2, alpha 1.
 __device__ __forceinline__ uint32_t mix32(uint32_t v) {
@@ -303,17 +377,6 @@ hipError_t launch_integrate(int tiles, int d, int xs, int js, int waves_per_bloc
 }
 
 bool integrate_variant_exists(int tiles, int d, int xs, int js) { return lookup(tiles, d, xs, js).single != nullptr; }
-
-hipError_t launch_integrate_map(int tiles, int d, int xs, int waves_per_block, const IntegArgs &a,
-                                hipStream_t stream, bool *supported) {
-    KernelFn fn = lookup(tiles, d, xs, 1);
-    *supported = fn.single_map != nullptr;
-    if (!fn.single_map) return hipSuccess;
-    const int reps_per_block = 16 * waves_per_block;
-    const int blocks = (a.r + reps_per_block - 1) / reps_per_block;
-    hipLaunchKernelGGL(fn.single_map, dim3(blocks), dim3(64 * waves_per_block), 0, stream, a);
-    return hipGetLastError();
-}
 
 bool map_variant_exists(int tiles, int d, int xs) { return lookup(tiles, d, xs, 1).persistent_map != nullptr; }
 

@@ -94,10 +94,49 @@ __device__ __forceinline__ void split8(const float (&v)[8], XSplit<XS> &out) {
     for (int k = 0; k < XS; ++k) out.t[k] = join4(t[k][0], t[k][1], t[k][2], t[k][3]);
 }
 
-// Loads one coupling value as float (0 outside the n x n matrix).
-__device__ __forceinline__ float j_at(const IntegArgs &a, int p, int q) {
-    if (p >= a.n || q >= a.n) return 0.0f;
-    return coupling(a.j, a.j_dtype, a.n, p, q);
+// The couplings J[p][q .. q+3] as float (0 outside the n x n matrix).  Four
+// columns inside the matrix are one load (4, 8 or 16 bytes, at the element
+// alignment); the last columns of a row are read one by one.
+__device__ __forceinline__ void j_at4(const IntegArgs &a, int p, int q, float (&v)[4]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) v[s] = 0.0f;
+    if (p >= a.n || q >= a.n) return;
+    if (q + 3 >= a.n) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            if (q + s < a.n) v[s] = coupling(a.j, a.j_dtype, a.n, p, q + s);
+        return;
+    }
+    const size_t i = (size_t)p * a.n + q;
+    switch (a.j_dtype) {
+        case CHYM_J_I8: {
+            uint32_t b;
+            __builtin_memcpy(&b, reinterpret_cast<const int8_t *>(a.j) + i, 4);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) v[s] = (float)(int8_t)(b >> (8 * s));
+            break;
+        }
+        case CHYM_J_F32: {
+            __builtin_memcpy(v, reinterpret_cast<const float *>(a.j) + i, 16);
+            break;
+        }
+        case CHYM_J_BF16: {
+            uint32_t b[2];
+            __builtin_memcpy(b, reinterpret_cast<const uint16_t *>(a.j) + i, 8);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) v[s] = __uint_as_float((s & 1) ? b[s >> 1] & 0xffff0000u : b[s >> 1] << 16);
+            break;
+        }
+        default: {
+            const uint8_t *j8 = reinterpret_cast<const uint8_t *>(a.j);
+            const uint32_t e = j8[(size_t)a.n * a.n + p];
+            uint32_t b;
+            __builtin_memcpy(&b, j8 + i, 4);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                v[s] = e == 0xffu ? __builtin_nanf("") : ldexpf(e4m3_value((b >> (8 * s)) & 0xffu), (int)e - 127);
+        }
+    }
 }
 
 // A fragment (I, c) for lane (i, g): slot s holds
@@ -106,18 +145,24 @@ template <int JS>
 __device__ __forceinline__ void j_fragment(const IntegArgs &a, int I, int c, int lane, bf16x8 (&f)[JS]) {
     const int i = lane & 15, g = lane >> 4;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        const float v = j_at(a, 16 * I + i, 32 * c + 16 * (s >> 2) + 4 * g + (s & 3));
-        if constexpr (JS == 1) {
-            f[0][s] = (__bf16)v;
-        } else {
-            const __bf16 h = (__bf16)v;
-            const float r1 = v - bf_to_f(h);
-            const __bf16 m = (__bf16)r1;
-            const float r2 = r1 - bf_to_f(m);
-            f[0][s] = h;
-            f[1][s] = m;
-            f[2][s] = (__bf16)r2;
+    for (int h = 0; h < 2; ++h) {
+        float v4[4];
+        j_at4(a, 16 * I + i, 32 * c + 16 * h + 4 * g, v4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int s = 4 * h + u;
+            const float v = v4[u];
+            if constexpr (JS == 1) {
+                f[0][s] = (__bf16)v;
+            } else {
+                const __bf16 hi = (__bf16)v;
+                const float r1 = v - bf_to_f(hi);
+                const __bf16 m = (__bf16)r1;
+                const float r2 = r1 - bf_to_f(m);
+                f[0][s] = hi;
+                f[1][s] = m;
+                f[2][s] = (__bf16)r2;
+            }
         }
     }
 }
@@ -389,12 +434,12 @@ __device__ __forceinline__ void integrate_group(const IntegArgs &a, int rep0, co
 }
 
 // One problem: wavefront w of the grid integrates replicas 16 w .. 16 w + 15.
-template <int NT, int D, int XS, int JS, bool MAP = false>
+template <int NT, int D, int XS, int JS>
 __global__ __launch_bounds__(256) void k_integrate_resident(IntegArgs a) {
     const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int rep0 = wave * 16;
     if (rep0 >= a.r) return;
-    integrate_group<NT, D, XS, JS, false, MAP>(a, rep0, nullptr);
+    integrate_group<NT, D, XS, JS, false>(a, rep0, nullptr);
 }
 
 // Many problems of one variant: a persistent grid whose wavefronts pop work
@@ -542,7 +587,6 @@ __device__ __forceinline__ void pipe_step(float (&x)[NT][D][4], f32x4 (&cur)[NT]
                                           XSplit<XS> (&bx)[2][D], const float (&ga_cur)[D], const float (&ga_prev)[D],
                                           const bf16x8 *jl, int lane, float base, float nbd, float ned) {
     constexpr int NC = (NT + 1) / 2;
-    constexpr int NP = JS == 1 ? XS : 6;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         const int bi = (P + c) & 1;
@@ -719,8 +763,7 @@ struct KernelSet {
     void (*persistent_lds)(const IntegArgs *, const int2 *, int, int *);   // two wavefronts per SIMD
     void (*persistent_lds1)(const IntegArgs *, const int2 *, int, int *);  // one wavefront per SIMD
     size_t lds_bytes;
-    void (*single_map)(IntegArgs);  // round-trip map form (single coupling term only)
-    void (*persistent_map)(const IntegArgs *, const int2 *, int, int *);  // same, many problems
+    void (*persistent_map)(const IntegArgs *, const int2 *, int, int *);  // round-trip map form, many problems
     void (*persistent_pipe)(const IntegArgs *, const int2 *, int, int *);  // pipelined, one wavefront per SIMD
     void (*persistent_lds3)(const IntegArgs *, const int2 *, int, int *);  // three wavefronts per SIMD
 };
@@ -747,11 +790,10 @@ KernelSet variant_or_null() {
         return KernelSet{k_integrate_resident<NT, D, XS, JS>, k_integrate_persistent<NT, D, XS, JS>,
                          k_integrate_persistent_lds<NT, D, XS, JS, 2>, k_integrate_persistent_lds<NT, D, XS, JS, 1>,
                          lds_j_bytes<NT, JS>(),
-                         (JS == 1 && NT <= kMapMaxTiles) ? k_integrate_resident<NT, D, XS, JS, true> : nullptr,
                          (JS == 1 && NT <= kMapMaxTiles) ? k_integrate_persistent<NT, D, XS, JS, true> : nullptr,
                          pipe_fn<NT, D, XS, JS>(), lds3_fn<NT, D, XS, JS>()};
     else
-        return KernelSet{nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr};
+        return KernelSet{nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
 }
 
 // One translation unit per (D, XS, JS) instantiates all tile counts.
@@ -770,7 +812,7 @@ KernelSet lookup_tiles(int tiles) {
         case 10: return variant_or_null<10, D, XS, JS>();
         case 11: return variant_or_null<11, D, XS, JS>();
         case 12: return variant_or_null<12, D, XS, JS>();
-        default: return KernelSet{nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr};
+        default: return KernelSet{nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
     }
 }
 
