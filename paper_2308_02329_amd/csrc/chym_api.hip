@@ -376,7 +376,7 @@ struct BatchLayout {
     int n_stage1 = 0, n_stage3 = 0;
     size_t off_tasks, off_items, off_counters, off_score, off_first, off_jfp, off_ncp, off_list, off_jf, total;
     int64_t total_replicas;
-    int max_nd;
+    size_t ising_lds, hs_lds;  // scoring kernels' LDS
     bool any_readout, any_ising, any_hs;
 };
 
@@ -482,16 +482,20 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         L->groups.push_back(g);
     }
     L->total_replicas = 0;
-    L->max_nd = 1;
+    L->ising_lds = L->hs_lds = 0;
     L->any_readout = L->any_ising = L->any_hs = false;
     for (int t = 0; t < n_tasks; ++t) {
         const chym_out &o = tasks[t].out;
         L->total_replicas += tasks[t].run.r;
         L->any_readout |= (o.spins || o.extra_frac || o.diverged) != 0;
-        L->any_ising |= (o.e_ising || o.e_ising_f64) != 0;
+        const chym_problem &pr = tasks[t].prob;
+        if (o.e_ising || o.e_ising_f64) {
+            L->any_ising = true;
+            L->ising_lds = std::max(L->ising_lds, chym::ising_score_lds(pr.n, pr.j_dtype));
+        }
         if (o.e_hs) {
             L->any_hs = true;
-            L->max_nd = std::max(L->max_nd, tasks[t].prob.n * tasks[t].prob.d);
+            L->hs_lds = std::max(L->hs_lds, chym::hs_score_lds(pr.n, pr.d, pr.j_dtype));
         }
     }
     const BatchTables T = batch_tables((size_t)n_tasks, L->items.size(), L->groups.size());
@@ -592,7 +596,7 @@ int issue_batch(const chym_batch *b, hipStream_t main, const std::vector<hipStre
     if (L.any_readout || L.any_ising || L.any_hs) {
         e = chym::launch_score_batched(reinterpret_cast<const chym::ScoreArgs *>(b->ws + L.off_score),
                                        reinterpret_cast<const int64_t *>(b->ws + L.off_first), (int)b->tasks.size(),
-                                       L.total_replicas, L.max_nd, L.any_readout, L.any_ising, L.any_hs, b->cus, main);
+                                       L.total_replicas, L.ising_lds, L.hs_lds, L.any_readout, L.any_ising, L.any_hs, b->cus, main);
         if (e != hipSuccess) return hip_fail(e, "batched scoring launch");
     }
     return CHYM_OK;

@@ -10,6 +10,8 @@ namespace chym {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(4))) double f64x4;
 
 // Value of an OCP E4M3 (e4m3fn) byte: sign, 4 exponent bits (bias 7), 3
 // mantissa bits; exponent field 0 holds the subnormals m * 2^-9; 0x7f and
@@ -92,6 +94,56 @@ __device__ __forceinline__ float coupling(const void *j, int j_dtype, int n, int
             return ldexpf(e4m3_value(b[i]), (int)e - 127);
         }
     }
+}
+
+// The couplings J[p][q .. q+3], all inside the n x n matrix, as float: one load
+// of 4, 8 or 16 bytes at the element alignment.
+__device__ __forceinline__ void coupling4_inside(const void *j, int j_dtype, int n, int p, int q, float (&v)[4]) {
+    const size_t i = (size_t)p * n + q;
+    switch (j_dtype) {
+        case CHYM_J_I8: {
+            uint32_t b;
+            __builtin_memcpy(&b, reinterpret_cast<const int8_t *>(j) + i, 4);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) v[s] = (float)(int8_t)(b >> (8 * s));
+            break;
+        }
+        case CHYM_J_F32: {
+            __builtin_memcpy(v, reinterpret_cast<const float *>(j) + i, 16);
+            break;
+        }
+        case CHYM_J_BF16: {
+            uint32_t b[2];
+            __builtin_memcpy(b, reinterpret_cast<const uint16_t *>(j) + i, 8);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) v[s] = __uint_as_float((s & 1) ? b[s >> 1] & 0xffff0000u : b[s >> 1] << 16);
+            break;
+        }
+        default: {
+            const uint8_t *j8 = reinterpret_cast<const uint8_t *>(j);
+            const uint32_t e = j8[(size_t)n * n + p];
+            uint32_t b;
+            __builtin_memcpy(&b, j8 + i, 4);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                v[s] = e == 0xffu ? __builtin_nanf("") : ldexpf(e4m3_value((b >> (8 * s)) & 0xffu), (int)e - 127);
+        }
+    }
+}
+
+// The same with 0 outside the matrix; the last columns of a row are read one
+// by one.
+__device__ __forceinline__ void coupling4(const void *j, int j_dtype, int n, int p, int q, float (&v)[4]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) v[s] = 0.0f;
+    if (p >= n || q >= n) return;
+    if (q + 3 < n) {
+        coupling4_inside(j, j_dtype, n, p, q, v);
+        return;
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+        if (q + s < n) v[s] = coupling(j, j_dtype, n, p, q + s);
 }
 
 // Largest row-tile count (16 rows per tile) of the register-resident
@@ -186,11 +238,16 @@ struct ScoreArgs {
     int32_t n, d, r, j_dtype;
 };
 
+// LDS one block needs for a task's float64 energies: the Ising energy of
+// couplings other than int8 (0 where it needs none), the hyperspin energy.
+size_t ising_score_lds(int n, int j_dtype);
+size_t hs_score_lds(int n, int d, int j_dtype);
 // Readout, Ising energy and hyperspin energy of every replica of every task
-// (first = replica prefix table, first[n_tasks] = total_replicas).
+// (first = replica prefix table, first[n_tasks] = total_replicas); ising_lds
+// and hs_lds: the largest of the above over the tasks that want the energy.
 hipError_t launch_score_batched(const ScoreArgs *tasks, const int64_t *first, int n_tasks, int64_t total_replicas,
-                                int max_nd, bool any_readout, bool any_ising, bool any_hs, int cus,
-                                hipStream_t stream);
+                                size_t ising_lds, size_t hs_lds, bool any_readout, bool any_ising, bool any_hs,
+                                int cus, hipStream_t stream);
 
 // Streamed-J slab integrator (large n).  Tiles of 16 rows; kSlabMaxLds
 // bounds the LDS operand area of one column slab (beyond it the float32 form

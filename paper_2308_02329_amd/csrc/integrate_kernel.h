@@ -94,51 +94,6 @@ __device__ __forceinline__ void split8(const float (&v)[8], XSplit<XS> &out) {
     for (int k = 0; k < XS; ++k) out.t[k] = join4(t[k][0], t[k][1], t[k][2], t[k][3]);
 }
 
-// The couplings J[p][q .. q+3] as float (0 outside the n x n matrix).  Four
-// columns inside the matrix are one load (4, 8 or 16 bytes, at the element
-// alignment); the last columns of a row are read one by one.
-__device__ __forceinline__ void j_at4(const IntegArgs &a, int p, int q, float (&v)[4]) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) v[s] = 0.0f;
-    if (p >= a.n || q >= a.n) return;
-    if (q + 3 >= a.n) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-            if (q + s < a.n) v[s] = coupling(a.j, a.j_dtype, a.n, p, q + s);
-        return;
-    }
-    const size_t i = (size_t)p * a.n + q;
-    switch (a.j_dtype) {
-        case CHYM_J_I8: {
-            uint32_t b;
-            __builtin_memcpy(&b, reinterpret_cast<const int8_t *>(a.j) + i, 4);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) v[s] = (float)(int8_t)(b >> (8 * s));
-            break;
-        }
-        case CHYM_J_F32: {
-            __builtin_memcpy(v, reinterpret_cast<const float *>(a.j) + i, 16);
-            break;
-        }
-        case CHYM_J_BF16: {
-            uint32_t b[2];
-            __builtin_memcpy(b, reinterpret_cast<const uint16_t *>(a.j) + i, 8);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) v[s] = __uint_as_float((s & 1) ? b[s >> 1] & 0xffff0000u : b[s >> 1] << 16);
-            break;
-        }
-        default: {
-            const uint8_t *j8 = reinterpret_cast<const uint8_t *>(a.j);
-            const uint32_t e = j8[(size_t)a.n * a.n + p];
-            uint32_t b;
-            __builtin_memcpy(&b, j8 + i, 4);
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-                v[s] = e == 0xffu ? __builtin_nanf("") : ldexpf(e4m3_value((b >> (8 * s)) & 0xffu), (int)e - 127);
-        }
-    }
-}
-
 // A fragment (I, c) for lane (i, g): slot s holds
 // J[16 I + i][32 c + 16 (s >> 2) + 4 g + (s & 3)], split into JS bf16 terms.
 template <int JS>
@@ -147,7 +102,7 @@ __device__ __forceinline__ void j_fragment(const IntegArgs &a, int I, int c, int
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         float v4[4];
-        j_at4(a, 16 * I + i, 32 * c + 16 * h + 4 * g, v4);
+        coupling4(a.j, a.j_dtype, a.n, 16 * I + i, 32 * c + 16 * h + 4 * g, v4);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int s = 4 * h + u;
