@@ -60,7 +60,7 @@ def kernel_name(tiles, d, precision, plan):
         return f"k_integrate_persistent_lds<{tiles}, {d}, {xs}, 1, 2>"
     if kind == 3:
         return f"k_integrate_persistent_lds<{tiles}, {d}, {xs}, 1, 1>"
-    return f"k_integrate_persistent<{tiles}, {d}, {xs}, 1, false>"  # false: the continuous-limit form
+    return f"k_integrate_persistent<{tiles}, {d}, {xs}, 1>"
 
 
 def parse():
@@ -589,7 +589,7 @@ def run_stats(args, torch, api, synth):
                        "round_trips": steps, "precision": "f32"},
             "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                          "frac": achieved / PEAK_BF16_TFLOPS, "traffic": None,
-                         "kernel": "k_integrate_persistent<7, 1, 3, 1, true>", "kernel_ms": ms1},
+                         "kernel": "k_integrate_team<1, 3, 1, 4, 2, true, true>", "kernel_ms": ms1},
             "map_batch_ms": {"d1": ms1, "d2": kms[2] / args.steps}}
 
 
@@ -648,7 +648,7 @@ def run_xy(args, torch, api, synth):
                        "n": n, "graphs": n_graphs, "runs": runs, "round_trips": steps, "precision": "f32"},
             "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                          "frac": achieved / PEAK_BF16_TFLOPS, "traffic": None,
-                         "kernel": "k_integrate_persistent<7, 2, 3, 1, true>", "kernel_ms": ms}}
+                         "kernel": "k_integrate_team<2, 3, 1, 4, 2, true, true>", "kernel_ms": ms}}
 
 
 def main():

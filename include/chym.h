@@ -211,14 +211,13 @@ typedef struct chym_map_problem {
 
 int chym_map_integrate(const chym_map_problem *prob, const chym_run *run, chym_stream_t stream);
 
-/* Many map problems, one persistent launch per kernel variant (row tiles,
+/* Many map problems, one launch per kernel variant (row tiles,
  * d, precision).  Paper: the statistics are gathered over N_g graphs x N_s
  * pump values x N_r repetitions of the map, all independent (statistics
  * paragraph, Figs. 3-4).  Each problem t is chym_map_integrate(&probs[t],
  * &runs[t]); results are bit-identical to it.  The workspace (device, 256-byte
- * aligned, size from chym_map_batch_workspace_size) receives the task table,
- * the work list of (task, 16-replica group) items, longest run first, and
- * one work counter per variant.  The host tables are copied on `stream`,
+ * aligned, size from chym_map_batch_workspace_size) receives the task table and
+ * the work list of (task, replica block) items, longest run first.  The host tables are copied on `stream`,
  * which is synchronized once before the launches are queued; the launches
  * then run asynchronously.  Calls that share a workspace must not overlap.
  * Errors name the offending task; nothing is launched if any task is
@@ -435,6 +434,11 @@ int chym_to_bf16(const float *src, uint16_t *dst, int32_t n, chym_stream_t strea
  * The table is process-wide and starts empty: CHYM_KERNEL_REGJ with 4 waves
  * per block for the register-resident variants, CHYM_KERNEL_SLAB with 16
  * waves up to 32 row tiles where built and 8 beyond for the streamed-J ones.
+ * Launches that leave the chip idle on these (few replicas in all tasks of a
+ * variant), and most streamed-J variants up to n = 256, run on the team
+ * integrator (rows of a problem over the wavefronts of a block) instead,
+ * unless chym_plan_set chose the kernel: entries of the autotuner and of plan
+ * files were measured with the chip full.
  * The single-problem calls (chym_integrate_ws, chym_solve_ws) use the
  * streamed-J entries too.  Plans change speed only, never results.
  */

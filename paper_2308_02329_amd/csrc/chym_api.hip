@@ -156,6 +156,7 @@ int check_variant(const chym_problem *prob, const chym_run *run) {
 }
 
 int slab_plan_waves(const Variant &v, int d);  // block size of the streamed-J kernel from the plan table
+bool plan_binds(const Variant &v, int d);      // a streamed-J variant's block size set by the caller
 
 int integrate_impl(const chym_problem *prob, const chym_run *run, hipStream_t stream, void *ws = nullptr,
                    size_t ws_bytes = 0) {
@@ -180,9 +181,13 @@ int integrate_impl(const chym_problem *prob, const chym_run *run, hipStream_t st
         if (e != hipSuccess) return hip_fail(e, "sparse integrate launch");
         return CHYM_OK;
     }
-    const int layout = chym::team_layout(v.tiles, prob->d, v.xs, v.js, run->r, false, cus);
-    if (layout != chym::kTeamNone) {
-        hipError_t e = chym::launch_integrate_team(layout, v.tiles, prob->d, v.xs, v.js, false, a, stream);
+    const int pack = chym::team_block_replicas(chym::kTeamPack, prob->d);
+    const int layout = chym::team_layout(v.tiles, prob->d, v.xs, v.js, (run->r + pack - 1) / pack, (run->r + 15) / 16,
+                                         false, false, cus);
+    if (layout != chym::kTeamNone && !plan_binds(v, prob->d)) {
+        const int rb = chym::team_block_replicas(layout, prob->d);
+        hipError_t e = chym::launch_integrate_team(layout, v.tiles, prob->d, v.xs, v.js, false, (run->r + rb - 1) / rb,
+                                                   a, nullptr, nullptr, stream);
         if (e != hipSuccess) return hip_fail(e, "integrate launch");
         return CHYM_OK;
     }
@@ -272,6 +277,10 @@ struct PlanValue {
     int kind;   // chym::kKernelRegJ / kKernelLdsJ / kKernelLdsJ1 / kKernelPipe / kKernelLdsJ3 / kKernelSlab
     int waves;  // wavefronts per block
     float ms;
+    // where the entry comes from: none; the autotuner or a plan file, measured
+    // with the chip full, so that launches that leave it idle may take the
+    // team integrator; the caller (chym_plan_set), whose choice stands
+    enum From { kDefault, kTuned, kSet } from;
 };
 
 // Streamed-J variants take the slab kernel; their plans choose its block
@@ -302,11 +311,24 @@ PlanValue plan_for(const VariantKey &k) {
     std::lock_guard<std::mutex> lk(g_plan_mu);
     auto it = g_plan.find(k);
     if (it != g_plan.end()) return it->second;
-    if (key_is_slab(k)) return PlanValue{kKernelSlab, default_slab_waves(k), 0.0f};
-    return PlanValue{chym::kKernelRegJ, kDefaultWaves, 0.0f};
+    if (key_is_slab(k)) return PlanValue{kKernelSlab, default_slab_waves(k), 0.0f, PlanValue::kDefault};
+    return PlanValue{chym::kKernelRegJ, kDefaultWaves, 0.0f, PlanValue::kDefault};
 }
 
 int slab_plan_waves(const Variant &v, int d) { return plan_for(key_of(v, d)).waves; }
+bool plan_binds(const Variant &v, int d) { return v.slab && plan_for(key_of(v, d)).from == PlanValue::kSet; }
+
+// Compute units of the current device (256, the full chip's, without one: the
+// layouts of tables built where no device is visible).
+int current_cus() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
+        (void)hipGetLastError();
+        return 256;
+    }
+    return cus;
+}
 
 int kind_of_code(int code) {
     switch (code) {
@@ -362,6 +384,7 @@ struct Group {
     Variant v;
     int d;
     int kind, waves;  // launch plan of this variant (resident kernels)
+    int team;         // layout of the team integrator, or chym::kTeamNone
     int item_off, n_items;
     int blocks;
     size_t lds;  // slab kernels: LDS operand area; gather kernel: the largest block's LDS
@@ -418,7 +441,18 @@ int validate_out(const chym_problem *prob, const chym_run *run, const chym_out *
 int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
     if (n_tasks < 1) return fail(CHYM_EINVAL, "n_tasks = %d must be >= 1", n_tasks);
     if (!tasks) return fail(CHYM_EINVAL, "tasks is NULL");
-    std::map<std::tuple<int, int, int, int, int>, std::vector<int2>> by_variant;  // (slab, tiles, d, xs, js)
+    // group key (kind, tiles, d, xs, js): kind 0 resident, 1 streamed-J, 2 sparse rows (one group per d)
+    typedef std::tuple<int, int, int, int, int> GroupKey;
+    auto group_of = [&](int t) {
+        const Variant v = variant_of(&tasks[t].prob, &tasks[t].run);
+        return v.ell ? GroupKey(2, 0, tasks[t].prob.d, 0, 0) : GroupKey((int)v.slab, v.tiles, tasks[t].prob.d, v.xs, v.js);
+    };
+    struct Load {
+        int64_t blocks = 0, waves = 0;  // packed blocks and 16-replica groups of the team integrator
+        int team = chym::kTeamNone;
+    };
+    std::map<GroupKey, Load> load;
+    std::map<GroupKey, std::vector<int2>> by_variant;
     for (int t = 0; t < n_tasks; ++t) {
         const chym_task &tk = tasks[t];
         int rc = validate_problem(&tk.prob);
@@ -429,17 +463,34 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
             std::string m = g_err;
             return fail(rc, "task %d: %s", t, m.c_str());
         }
+        if (tk.run.steps == 0 || variant_of(&tk.prob, &tk.run).ell) continue;
+        Load &ld = load[group_of(t)];
+        const int pack = chym::team_block_replicas(chym::kTeamPack, tk.prob.d);
+        ld.blocks += (tk.run.r + pack - 1) / pack;
+        ld.waves += (tk.run.r + 15) / 16;
+    }
+    const int cus = current_cus();
+    for (auto &kv : load) {
+        const int tiles = std::get<1>(kv.first), d = std::get<2>(kv.first), xs = std::get<3>(kv.first);
+        const int js = std::get<4>(kv.first);
+        const PlanValue pv = plan_for(std::make_tuple(tiles, d, xs, js));
+        if (pv.from != PlanValue::kSet)
+            kv.second.team = chym::team_layout(tiles, d, xs, js, kv.second.blocks, kv.second.waves, false,
+                                               pv.from == PlanValue::kTuned, cus);
+    }
+    for (int t = 0; t < n_tasks; ++t) {
+        const chym_task &tk = tasks[t];
         const Variant v = variant_of(&tk.prob, &tk.run);
-        const VariantKey key = key_of(v, tk.prob.d);
-        // group key (kind, tiles, d, xs, js): kind 0 resident, 1 streamed-J, 2 sparse rows (one group per d)
-        auto &lst = by_variant[v.ell ? std::make_tuple(2, 0, tk.prob.d, 0, 0)
-                                     : std::make_tuple((int)v.slab, v.tiles, tk.prob.d, v.xs, v.js)];
+        const GroupKey gk = group_of(t);
+        auto &lst = by_variant[gk];
         if (tk.run.steps == 0) continue;
         int slab = 16;
         if (v.ell) {
             slab = chym::ell_replicas_per_block(tk.prob.n, tk.prob.d);
+        } else if (load[gk].team != chym::kTeamNone) {
+            slab = chym::team_block_replicas(load[gk].team, tk.prob.d);
         } else if (!v.slab) {
-            const PlanValue pv = plan_for(key);
+            const PlanValue pv = plan_for(key_of(v, tk.prob.d));
             slab = pv.kind != chym::kKernelRegJ ? 16 * pv.waves : 16;
         }
         const int slabs = (tk.run.r + slab - 1) / slab;
@@ -462,7 +513,11 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         g.v.xs = std::get<3>(kv.first);
         g.v.js = std::get<4>(kv.first);
         g.lds = 0;
-        if (g.v.ell) {
+        g.team = g.v.ell ? chym::kTeamNone : load[kv.first].team;
+        if (g.team != chym::kTeamNone) {
+            g.kind = -3;
+            g.waves = 0;
+        } else if (g.v.ell) {
             g.kind = -2;
             g.waves = 16;
             for (const int2 &it : lst) g.lds = std::max(g.lds, chym::ell_lds_bytes(tasks[it.x].prob.n, g.d));
@@ -515,7 +570,7 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
     size_t off = L->off_jf;
     for (int t = 0; t < n_tasks; ++t) {
         const Variant v = variant_of(&tasks[t].prob, &tasks[t].run);
-        if (!v.slab || tasks[t].run.steps == 0) continue;
+        if (!v.slab || tasks[t].run.steps == 0 || load[group_of(t)].team != chym::kTeamNone) continue;
         L->jf_off[t] = off;
         L->ncp[t] = (v.tiles + 1) / 2;
         off += align_up(slab_ws_bytes(v));
@@ -575,7 +630,10 @@ int issue_batch(const chym_batch *b, hipStream_t main, const std::vector<hipStre
             e = hipStreamWaitEvent(s, (*events)[0], 0);
             if (e != hipSuccess) return hip_fail(e, "hipStreamWaitEvent");
         }
-        if (g.v.ell)
+        if (g.team != chym::kTeamNone)
+            e = chym::launch_integrate_team(g.team, g.v.tiles, g.d, g.v.xs, g.v.js, false, g.n_items, chym::IntegArgs{},
+                                            tasks_d, items_d + g.item_off, s);
+        else if (g.v.ell)
             e = chym::launch_integrate_ell_persistent(g.d, g.blocks, g.lds, tasks_d, items_d + g.item_off, g.n_items,
                                                       counters + gi, s);
         else if (g.v.slab)
@@ -663,20 +721,20 @@ int map_setup(const chym_map_problem *m, const chym_run *run, MapTask *t) {
 }
 
 struct MapGroup {
-    int tiles, d, xs, item_off, n_items;
+    int tiles, d, xs, team, item_off, n_items;  // team: layout of the team integrator
 };
 
 struct MapBatchLayout {
     std::vector<chym::IntegArgs> args;
-    std::vector<int2> items;  // (task, 16-replica group), grouped by variant, longest task first
+    std::vector<int2> items;  // (task, replica block), grouped by variant, longest task first
     std::vector<MapGroup> groups;
-    size_t off_tasks, off_items, off_counters, total;
+    size_t off_tasks, off_items, total;
 };
 
 int map_batch_layout(const chym_map_problem *probs, const chym_run *runs, int32_t n_tasks, MapBatchLayout *L) {
     if (n_tasks < 1) return fail(CHYM_EINVAL, "n_tasks = %d must be >= 1", n_tasks);
     if (!probs || !runs) return fail(CHYM_EINVAL, "problems or runs is NULL");
-    std::map<std::tuple<int, int, int>, std::vector<int2>> by_variant;  // (tiles, d, xs)
+    std::map<std::tuple<int, int, int>, std::vector<int>> by_variant;  // (tiles, d, xs): tasks
     L->args.resize(n_tasks);
     for (int t = 0; t < n_tasks; ++t) {
         MapTask mt;
@@ -686,26 +744,33 @@ int map_batch_layout(const chym_map_problem *probs, const chym_run *runs, int32_
             return fail(rc, "task %d: %s", t, m.c_str());
         }
         L->args[t] = mt.a;
-        auto &lst = by_variant[std::make_tuple(mt.tiles, probs[t].d, mt.xs)];
-        if (runs[t].steps == 0) continue;
-        for (int g = 0; g < (runs[t].r + 15) / 16; ++g) lst.push_back(make_int2(t, g));
+        if (runs[t].steps > 0) by_variant[std::make_tuple(mt.tiles, probs[t].d, mt.xs)].push_back(t);
     }
     L->items.clear();
     L->groups.clear();
+    const int cus = current_cus();
     for (auto &kv : by_variant) {
         auto &lst = kv.second;
-        if (lst.empty()) continue;
-        std::stable_sort(lst.begin(), lst.end(),
-                         [&](const int2 &a, const int2 &b) { return runs[a.x].steps > runs[b.x].steps; });
-        MapGroup g{std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first), (int)L->items.size(),
-                   (int)lst.size()};
-        L->items.insert(L->items.end(), lst.begin(), lst.end());
+        const int tiles = std::get<0>(kv.first), d = std::get<1>(kv.first), xs = std::get<2>(kv.first);
+        std::stable_sort(lst.begin(), lst.end(), [&](int a, int b) { return runs[a].steps > runs[b].steps; });
+        const int pack = chym::team_block_replicas(chym::kTeamPack, d);
+        int64_t blocks = 0, waves = 0;
+        for (int t : lst) {
+            blocks += (runs[t].r + pack - 1) / pack;
+            waves += (runs[t].r + 15) / 16;
+        }
+        const int team = chym::team_layout(tiles, d, xs, 1, blocks, waves, true, false, cus);
+        if (team == chym::kTeamNone) return fail(CHYM_EUNSUPPORTED, "no map variant for %d row tiles, d = %d", tiles, d);
+        const int rb = chym::team_block_replicas(team, d);
+        MapGroup g{tiles, d, xs, team, (int)L->items.size(), 0};
+        for (int t : lst)
+            for (int k = 0; k < (runs[t].r + rb - 1) / rb; ++k) L->items.push_back(make_int2(t, k));
+        g.n_items = (int)L->items.size() - g.item_off;
         L->groups.push_back(g);
     }
     L->off_tasks = 0;
     L->off_items = align_up(sizeof(chym::IntegArgs) * (size_t)n_tasks);
-    L->off_counters = L->off_items + align_up(sizeof(int2) * std::max<size_t>(1, L->items.size()));
-    L->total = L->off_counters + align_up(sizeof(int) * std::max<size_t>(1, L->groups.size()));
+    L->total = L->off_items + align_up(sizeof(int2) * std::max<size_t>(1, L->items.size()));
     return CHYM_OK;
 }
 
@@ -741,7 +806,7 @@ int batch_build(const chym_task *tasks, int32_t n_tasks, void *workspace, size_t
     b->cus = cus;
     for (Group &g : b->layout.groups) {
         int per_cu = 0;
-        if (e == hipSuccess) {
+        if (e == hipSuccess && g.team == chym::kTeamNone) {
             if (g.v.ell) e = chym::ell_persistent_occupancy(g.d, g.lds, &per_cu);
             else if (g.v.slab) e = chym::slab_occupancy(g.v.tiles, g.d, g.v.xs, g.v.js, g.waves, g.lds, &per_cu);
             else e = chym::persistent_occupancy(g.v.tiles, g.d, g.v.xs, g.v.js, g.kind, g.waves, &per_cu);
@@ -871,9 +936,13 @@ int chym_map_integrate(const chym_map_problem *m, const chym_run *run, chym_stre
     int cus = 0;
     rc = check_device(&cus);
     if (rc) return rc;
-    const int layout = chym::team_layout(t.tiles, m->d, t.xs, 1, run->r, true, cus);
+    const int pack = chym::team_block_replicas(chym::kTeamPack, m->d);
+    const int layout = chym::team_layout(t.tiles, m->d, t.xs, 1, (run->r + pack - 1) / pack, (run->r + 15) / 16, true,
+                                         false, cus);
     if (layout == chym::kTeamNone) return fail(CHYM_EUNSUPPORTED, "no map variant for n = %d, d = %d", m->n, m->d);
-    hipError_t e = chym::launch_integrate_team(layout, t.tiles, m->d, t.xs, 1, true, t.a, (hipStream_t)stream);
+    const int rb = chym::team_block_replicas(layout, m->d);
+    hipError_t e = chym::launch_integrate_team(layout, t.tiles, m->d, t.xs, 1, true, (run->r + rb - 1) / rb, t.a,
+                                               nullptr, nullptr, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "map integrate launch");
     return CHYM_OK;
 }
@@ -902,31 +971,20 @@ int chym_map_batch(const chym_map_problem *probs, const chym_run *runs, int32_t 
     if (rc) return rc;
     const hipStream_t st = (hipStream_t)stream;
     char *ws = static_cast<char *>(workspace);
-    int dev = 0, cus = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     // The host tables are temporaries: copy them on the stream and wait for
     // the copy before they go out of scope.
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ws + L.off_tasks, L.args.data(), sizeof(chym::IntegArgs) * L.args.size(),
-                           hipMemcpyHostToDevice, st);
+    hipError_t e = hipMemcpyAsync(ws + L.off_tasks, L.args.data(), sizeof(chym::IntegArgs) * L.args.size(),
+                                  hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
         e = hipMemcpyAsync(ws + L.off_items, L.items.data(), sizeof(int2) * L.items.size(), hipMemcpyHostToDevice,
                            st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    int *counters = reinterpret_cast<int *>(ws + L.off_counters);
-    if (e == hipSuccess) e = chym::launch_zero_counters(counters, (int)L.groups.size(), st);
     const chym::IntegArgs *tasks_d = reinterpret_cast<const chym::IntegArgs *>(ws + L.off_tasks);
     const int2 *items_d = reinterpret_cast<const int2 *>(ws + L.off_items);
     for (size_t gi = 0; gi < L.groups.size() && e == hipSuccess; ++gi) {
         const MapGroup &g = L.groups[gi];
-        int per_cu = 0;
-        e = chym::map_persistent_occupancy(g.tiles, g.d, g.xs, &per_cu);
-        if (e != hipSuccess) break;
-        const int need = (g.n_items + kPersistentWaves - 1) / kPersistentWaves;
-        const int blocks = std::max(1, std::min(need, std::max(1, per_cu) * cus));
-        e = chym::launch_integrate_map_persistent(g.tiles, g.d, g.xs, blocks, tasks_d, items_d + g.item_off,
-                                                  g.n_items, counters + gi, st);
+        e = chym::launch_integrate_team(g.team, g.tiles, g.d, g.xs, 1, true, g.n_items, chym::IntegArgs{}, tasks_d,
+                                        items_d + g.item_off, st);
     }
     return e == hipSuccess ? CHYM_OK : hip_fail(e, "map batch launch");
 }
@@ -1143,7 +1201,7 @@ int chym_plan_set(const chym_plan_entry *e) {
             return fail(CHYM_EUNSUPPORTED, "kernel = %d is not built for n = %d, d = %d in this form", e->kernel, e->n,
                         e->d);
     }
-    g_plan[k] = PlanValue{kind_of_code(e->kernel), e->waves, e->ms};
+    g_plan[k] = PlanValue{kind_of_code(e->kernel), e->waves, e->ms, PlanValue::kSet};
     return CHYM_OK;
 }
 
@@ -1238,14 +1296,14 @@ int chym_plan_autotune(int32_t n, int32_t d, int32_t precision, int32_t j_dtype,
         had = it != g_plan.end();
         if (had) saved = it->second;
     }
-    const PlanValue all_cands[] = {{chym::kKernelRegJ, 4, 0.f},
-                                   {chym::kKernelLdsJ, 2, 0.f},
-                                   {chym::kKernelLdsJ, 4, 0.f},
-                                   {chym::kKernelLdsJ1, 4, 0.f},
-                                   {chym::kKernelPipe, 4, 0.f},
-                                   {chym::kKernelLdsJ3, 4, 0.f},
-                                   {kKernelSlab, chym::kSlabWaves8, 0.f},
-                                   {kKernelSlab, chym::kSlabWaves16, 0.f}};
+    const PlanValue all_cands[] = {{chym::kKernelRegJ, 4, 0.f, PlanValue::kSet},
+                                   {chym::kKernelLdsJ, 2, 0.f, PlanValue::kSet},
+                                   {chym::kKernelLdsJ, 4, 0.f, PlanValue::kSet},
+                                   {chym::kKernelLdsJ1, 4, 0.f, PlanValue::kSet},
+                                   {chym::kKernelPipe, 4, 0.f, PlanValue::kSet},
+                                   {chym::kKernelLdsJ3, 4, 0.f, PlanValue::kSet},
+                                   {kKernelSlab, chym::kSlabWaves8, 0.f, PlanValue::kSet},
+                                   {kKernelSlab, chym::kSlabWaves16, 0.f, PlanValue::kSet}};
     PlanValue cands[sizeof(all_cands) / sizeof(all_cands[0])];
     int kCands = 0;
     const bool slab = key_is_slab(key);
@@ -1313,6 +1371,7 @@ int chym_plan_autotune(int32_t n, int32_t d, int32_t precision, int32_t j_dtype,
         } else {
             PlanValue pv = cands[best_i];
             pv.ms = best_ms;
+            pv.from = PlanValue::kTuned;
             g_plan[key] = pv;
         }
     }
@@ -1517,7 +1576,7 @@ int chym_plan_load(const char *path) {
             return fail(CHYM_EINVAL, "%s:%d: kernel %d does not run %d tiles at d = %d in this form", path, lineno,
                         kernel, t, d);
         }
-        got.push_back({k, PlanValue{kind_of_code(kernel), waves, ms}});
+        got.push_back({k, PlanValue{kind_of_code(kernel), waves, ms, PlanValue::kTuned}});
     }
     fclose(f);
     std::lock_guard<std::mutex> lk(g_plan_mu);

@@ -167,27 +167,25 @@ struct IntegArgs {
 // variant; returns hipSuccess or the launch error.
 hipError_t launch_integrate(int tiles, int d, int xs, int js, int waves_per_block,
                             const IntegArgs &a, hipStream_t stream, bool *supported);
-// The round-trip map form (single coupling term only), up to this many row
-// tiles (the medium's gain per amplitude needs registers the largest
-// register-resident shapes do not have).
+// The round-trip map form (single coupling term only) runs up to this many row
+// tiles.
 constexpr int kMapMaxTiles = 7;
-// Many map problems of one variant (register-resident kernels): a persistent grid of 256-thread blocks
-// whose wavefronts pop items (task, 16-replica group) from *counter (zero at
-// launch) until n_items are taken.
-bool map_variant_exists(int tiles, int d, int xs);
-hipError_t map_persistent_occupancy(int tiles, int d, int xs, int *blocks_per_cu);
-hipError_t launch_integrate_map_persistent(int tiles, int d, int xs, int blocks, const IntegArgs *tasks,
-                                           const int2 *items, int n_items, int *counter, hipStream_t stream);
 bool integrate_variant_exists(int tiles, int d, int xs, int js);
 // Team integrator (a problem's row tiles spread over the wavefronts of a
-// block): the layout to take for r replicas on a GPU of cus compute units, or
-// kTeamNone where another integrator is faster; and its launch.
+// block): the layout to take for `blocks` packed blocks, that is `waves` groups
+// of 16 replicas, on a GPU of cus compute units, or kTeamNone where another
+// integrator is faster.  tuned: the other integrator is a plan that the
+// autotuner chose (a register-resident variant's; else the default one).
 constexpr int kTeamNone = 0;
 constexpr int kTeamPack = 1;   // 16 columns per block
 constexpr int kTeamPlane = 2;  // 16 replicas x d planes per block
-int team_layout(int tiles, int d, int xs, int js, int64_t r, bool map, int cus);
-hipError_t launch_integrate_team(int layout, int tiles, int d, int xs, int js, bool map, const IntegArgs &a,
-                                 hipStream_t stream);
+int team_layout(int tiles, int d, int xs, int js, int64_t blocks, int64_t waves, bool map, bool tuned, int cus);
+// Replicas per block of a layout (0 for kTeamNone).
+int team_block_replicas(int layout, int d);
+// One problem (items = NULL, `blocks` of its replica blocks), or n blocks'
+// items (task, replica block) of many problems of one shape.
+hipError_t launch_integrate_team(int layout, int tiles, int d, int xs, int js, bool map, int blocks,
+                                 const IntegArgs &one, const IntegArgs *tasks, const int2 *items, hipStream_t stream);
 // Persistent kernel kinds: J gathered into each wavefront's registers, work
 // items of 16 replicas; or J staged in LDS per block, work items of
 // 16 * waves_per_block replicas.

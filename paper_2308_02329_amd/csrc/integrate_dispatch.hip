@@ -14,7 +14,7 @@ static KernelFn lookup(int tiles, int d, int xs, int js) {
     CHYM_PICK(3, 3, 1) CHYM_PICK(3, 1, 1) CHYM_PICK(3, 3, 3)
     CHYM_PICK(4, 3, 1) CHYM_PICK(4, 1, 1) CHYM_PICK(4, 3, 3)
 #undef CHYM_PICK
-    return KernelSet{nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
+    return KernelSet{nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr};
 }
 
 int resident_tile_limit(int d, int xs, int js) {
@@ -250,46 +250,47 @@ static TeamFn lookup_team(int tiles, int d, int xs, int js, bool pack, bool map)
 // level with it.  Against one wavefront per 16 replicas both lose once those
 // fill the SIMDs: the wave's time goes up in steps of 16384 replicas, the
 // team's in proportion, so the line is drawn at 0.9 of a full step (0.7 with
-// three wavefronts on four SIMDs).  The map takes the team at every size: the
+// three wavefronts on four SIMDs; 0.6 of the first against a tuned plan, which
+// overlaps two or three wavefronts per SIMD at full load).  The map takes the team at every size: the
 // medium's gain is vector work, which one wavefront per SIMD cannot overlap
 // with its products (N = 100, D = 3, 65536 replicas: 28.2 us a step, plane
 // 23.4).  Against the streamed-J kernel both layouts win at every replica
 // count, except where no plane layout is built (its operand does not fit LDS
 // twice: float32 at D = 4 beyond 12 tiles) and J is one term: there packed
 // blocks are 5-10% slower beyond two to a CU.
-int team_layout(int tiles, int d, int xs, int js, int64_t r, bool map, int cus) {
+int team_layout(int tiles, int d, int xs, int js, int64_t blocks, int64_t waves, bool map, bool tuned, int cus) {
     if (!lookup_team(tiles, d, xs, js, true, map)) return kTeamNone;
     const int nc = (tiles + 1) / 2;
     const bool wave = map ? tiles <= kMapMaxTiles : tiles <= resident_tile_limit(d, xs, js);
     if (nc == 1 && d == 1 && !map) return kTeamNone;  // the same work in the same single wavefront
-    if (wave && !map && nc > 1) {
-        const int64_t full = (int64_t)4 * cus * 16;
-        const int64_t steps = (r + full - 1) / full;
-        if (10 * r > (nc == 3 ? 7 : 9) * steps * full) return kTeamNone;
+    if (wave && !map && (nc > 1 || tuned)) {
+        const int64_t full = (int64_t)4 * cus;
+        const int64_t steps = tuned ? 1 : (waves + full - 1) / full;
+        if (10 * waves > (tuned ? 6 : nc == 3 ? 7 : 9) * steps * full) return kTeamNone;
     }
     const bool plane = lookup_team(tiles, d, xs, js, false, map) != nullptr;
-    const int rp = team_replicas(d, true);
-    const int64_t per_cu = ((r + rp - 1) / rp + cus - 1) / cus;  // packed blocks
+    const int64_t per_cu = (blocks + cus - 1) / cus;
     if (per_cu <= (nc == 1 ? 8 : nc == 2 ? 4 : 2) * (map ? 2 : 1)) return kTeamPack;
     if (!wave && !plane && d > 1 && js == 1) return kTeamNone;
     return plane && (nc == 1 || d == 3 || xs == 1) ? kTeamPlane : kTeamPack;
 }
 
-hipError_t launch_integrate_team(int layout, int tiles, int d, int xs, int js, bool map, const IntegArgs &a,
-                                 hipStream_t stream) {
+int team_block_replicas(int layout, int d) { return layout == kTeamNone ? 0 : team_replicas(d, layout == kTeamPack); }
+
+hipError_t launch_integrate_team(int layout, int tiles, int d, int xs, int js, bool map, int blocks,
+                                 const IntegArgs &one, const IntegArgs *tasks, const int2 *items, hipStream_t stream) {
     const bool pack = layout == kTeamPack;
     TeamFn fn = lookup_team(tiles, d, xs, js, pack, map);
     if (!fn) return hipErrorInvalidDeviceFunction;
     const int nc = (tiles + 1) / 2;
-    const int rb = team_replicas(d, pack);
     const size_t lds = team_lds_bytes(nc, d, xs, pack);
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(fn, dim3((a.r + rb - 1) / rb), dim3(64 * team_waves(nc, team_tiles(tiles, xs, pack))), lds,
-                       stream, a);
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(64 * team_waves(nc, team_tiles(tiles, xs, pack))), lds, stream, one, tasks,
+                       items);
     return hipGetLastError();
 }
 
@@ -377,23 +378,6 @@ hipError_t launch_integrate(int tiles, int d, int xs, int js, int waves_per_bloc
 }
 
 bool integrate_variant_exists(int tiles, int d, int xs, int js) { return lookup(tiles, d, xs, js).single != nullptr; }
-
-bool map_variant_exists(int tiles, int d, int xs) { return lookup(tiles, d, xs, 1).persistent_map != nullptr; }
-
-hipError_t map_persistent_occupancy(int tiles, int d, int xs, int *blocks_per_cu) {
-    KernelFn fn = lookup(tiles, d, xs, 1);
-    *blocks_per_cu = 0;
-    if (!fn.persistent_map) return hipErrorInvalidDeviceFunction;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, fn.persistent_map, 256, 0);
-}
-
-hipError_t launch_integrate_map_persistent(int tiles, int d, int xs, int blocks, const IntegArgs *tasks,
-                                           const int2 *items, int n_items, int *counter, hipStream_t stream) {
-    KernelFn fn = lookup(tiles, d, xs, 1);
-    if (!fn.persistent_map) return hipErrorInvalidDeviceFunction;
-    hipLaunchKernelGGL(fn.persistent_map, dim3(blocks), dim3(256), 0, stream, tasks, items, n_items, counter);
-    return hipGetLastError();
-}
 
 static void (*lds_kernel(const KernelFn &fn, int kind))(const IntegArgs *, const int2 *, int, int *) {
     switch (kind) {

@@ -137,31 +137,10 @@ __device__ __forceinline__ void stage_j(const IntegArgs &a, bf16x8 *jl) {
     }
 }
 
-// Gain of the nonlinear medium for a field of amplitude A under pump h:
-// K = P / (P cosh(kl P) - h sinh(kl P)), P = sqrt(h^2 + A^2), written as
-// 2 P e / ((P + h) + (P - h) e^2) with e = exp(kl P); with P - h = A^2 / (P + h)
-// and both terms multiplied by s = P + h this is 2 P e s / (s^2 + A^2 e^2),
-// which has no cancellation for h >= 0 and needs one reciprocal.  The square
-// root, reciprocal and exponential are the hardware's (each within about
-// 1 ulp); kl2 = kl log2(e).
-__device__ __forceinline__ float nlm_gain(float A, float h, float kl2) {
-    const float A2 = A * A;
-    const float P = __builtin_amdgcn_sqrtf(fmaf(h, h, A2));
-    const float s = P + h;
-    if (!(s > 0.0f)) return 1.0f;  // A = h = 0: the medium is transparent
-    const float e = __builtin_amdgcn_exp2f(kl2 * P);
-    const float den = fmaf(A2, e * e, s * s);
-    return (2.0f * P * e * s) * __builtin_amdgcn_rcpf(den);
-}
-
 // Integrates the 16 replicas rep0 .. rep0+15 of problem a for a.steps steps.
 // Called by one whole wavefront.  JLDS: J fragments are read from the
 // block's LDS copy every step; otherwise they are gathered into registers.
-// MAP: the round-trip map of Eq. (2) instead of its continuous limit: every
-// amplitude first passes the medium (A <- K(A) A, pump h = pump[replica]),
-// then the same update runs with the map's coefficients, which the host puts
-// in eps, btil, eta and c0 (dt = 1).
-template <int NT, int D, int XS, int JS, bool JLDS, bool MAP = false>
+template <int NT, int D, int XS, int JS, bool JLDS>
 __device__ __forceinline__ void integrate_group(const IntegArgs &a, int rep0, const bf16x8 *jl) {
     constexpr int NC = (NT + 1) / 2;
     const int n = a.n;
@@ -197,10 +176,7 @@ __device__ __forceinline__ void integrate_group(const IntegArgs &a, int rep0, co
             for (int mu = 0; mu < D; ++mu) x[I][mu][v] = ok ? a.x[((size_t)p * r + rep) * D + mu] : 0.0f;
         }
 
-    // 1 + dt (r_i - 1); for the map the constant (1 - loss)(1 - b), and its pump h
-    const float base = valid ? (MAP ? a.c0 : fmaf(a.dt, a.pump[rep] - 1.0f, 1.0f)) : 0.0f;
-    const float hmap = (MAP && valid) ? a.pump[rep] : 0.0f;
-    const float kl2 = a.kl * 1.44269504088896340736f;  // kl log2(e)
+    const float base = valid ? fmaf(a.dt, a.pump[rep] - 1.0f, 1.0f) : 0.0f;  // 1 + dt (r_i - 1)
     const float nbd = -(a.dt * a.btil);
     const float ned = -(a.dt * a.eta);
     const float dte = a.dt * a.eps;
@@ -214,7 +190,7 @@ __device__ __forceinline__ void integrate_group(const IntegArgs &a, int rep0, co
     // hoisted into an earlier chunk.  The arithmetic and every summation
     // order are unchanged, so the result is bit-identical.  At D = 2 the same
     // order measured 4% faster; at D = 4 slower.
-    constexpr bool CO = JLDS && (D == 2 || D == 3) && !MAP;
+    constexpr bool CO = JLDS && (D == 2 || D == 3);
 
     for (int k = 0; k < a.steps; ++k) {
             if constexpr (JLDS) {
@@ -251,11 +227,6 @@ __device__ __forceinline__ void integrate_group(const IntegArgs &a, int rep0, co
                     if (I < NT && !CO) {
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            if constexpr (MAP) {
-#pragma unroll
-                                for (int mu = 0; mu < D; ++mu)
-                                    x[I][mu][v] = nlm_gain(x[I][mu][v], hmap, kl2) * x[I][mu][v];
-                            }
                             float x2[D];
 #pragma unroll
                             for (int mu = 0; mu < D; ++mu) x2[mu] = x[I][mu][v] * x[I][mu][v];
@@ -400,9 +371,8 @@ __global__ __launch_bounds__(256) void k_integrate_resident(IntegArgs a) {
 // Many problems of one variant: a persistent grid whose wavefronts pop work
 // items (problem, 16-replica group) from a counter until the list is empty.
 // Items are listed longest first by the host.  The counter must be zero at
-// launch; the host zeroes it with k_zero_counters in the same stream.  MAP
-// selects the round-trip map of Eq. (2) instead of its continuous limit.
-template <int NT, int D, int XS, int JS, bool MAP = false>
+// launch; the host zeroes it with k_zero_counters in the same stream.
+template <int NT, int D, int XS, int JS>
 __global__ __launch_bounds__(256) void k_integrate_persistent(const IntegArgs *__restrict__ tasks,
                                                               const int2 *__restrict__ items, int n_items,
                                                               int *__restrict__ counter) {
@@ -415,7 +385,7 @@ __global__ __launch_bounds__(256) void k_integrate_persistent(const IntegArgs *_
         if (it >= n_items) break;
         const int2 w = items[it];
         const IntegArgs a = tasks[w.x];
-        integrate_group<NT, D, XS, JS, false, MAP>(a, w.y * 16, nullptr);
+        integrate_group<NT, D, XS, JS, false>(a, w.y * 16, nullptr);
     }
 }
 
@@ -718,7 +688,6 @@ struct KernelSet {
     void (*persistent_lds)(const IntegArgs *, const int2 *, int, int *);   // two wavefronts per SIMD
     void (*persistent_lds1)(const IntegArgs *, const int2 *, int, int *);  // one wavefront per SIMD
     size_t lds_bytes;
-    void (*persistent_map)(const IntegArgs *, const int2 *, int, int *);  // round-trip map form, many problems
     void (*persistent_pipe)(const IntegArgs *, const int2 *, int, int *);  // pipelined, one wavefront per SIMD
     void (*persistent_lds3)(const IntegArgs *, const int2 *, int, int *);  // three wavefronts per SIMD
 };
@@ -745,10 +714,9 @@ KernelSet variant_or_null() {
         return KernelSet{k_integrate_resident<NT, D, XS, JS>, k_integrate_persistent<NT, D, XS, JS>,
                          k_integrate_persistent_lds<NT, D, XS, JS, 2>, k_integrate_persistent_lds<NT, D, XS, JS, 1>,
                          lds_j_bytes<NT, JS>(),
-                         (JS == 1 && NT <= kMapMaxTiles) ? k_integrate_persistent<NT, D, XS, JS, true> : nullptr,
                          pipe_fn<NT, D, XS, JS>(), lds3_fn<NT, D, XS, JS>()};
     else
-        return KernelSet{nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
+        return KernelSet{nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr};
 }
 
 // One translation unit per (D, XS, JS) instantiates all tile counts.
@@ -767,7 +735,7 @@ KernelSet lookup_tiles(int tiles) {
         case 10: return variant_or_null<10, D, XS, JS>();
         case 11: return variant_or_null<11, D, XS, JS>();
         case 12: return variant_or_null<12, D, XS, JS>();
-        default: return KernelSet{nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
+        default: return KernelSet{nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr};
     }
 }
 

@@ -73,6 +73,23 @@ __device__ __forceinline__ float quad_norm(float x2) {
     return s;
 }
 
+// Gain of the nonlinear medium for a field of amplitude A under pump h:
+// K = P / (P cosh(kl P) - h sinh(kl P)), P = sqrt(h^2 + A^2), written as
+// 2 P e / ((P + h) + (P - h) e^2) with e = exp(kl P); with P - h = A^2 / (P + h)
+// and both terms multiplied by s = P + h this is 2 P e s / (s^2 + A^2 e^2),
+// which has no cancellation for h >= 0 and needs one reciprocal.  The square
+// root, reciprocal and exponential are the hardware's (each within about
+// 1 ulp); kl2 = kl log2(e).
+__device__ __forceinline__ float nlm_gain(float A, float h, float kl2) {
+    const float A2 = A * A;
+    const float P = __builtin_amdgcn_sqrtf(fmaf(h, h, A2));
+    const float s = P + h;
+    if (!(s > 0.0f)) return 1.0f;  // A = h = 0: the medium is transparent
+    const float e = __builtin_amdgcn_exp2f(kl2 * P);
+    const float den = fmaf(A2, e * e, s * s);
+    return (2.0f * P * e * s) * __builtin_amdgcn_rcpf(den);
+}
+
 // Writes the operand terms of one tile and plane (the lane's four rows, v) into
 // the tile's half of the fragments f[64 t], t < XS.
 template <int XS>
@@ -87,7 +104,10 @@ __device__ __forceinline__ void team_write_half(const float (&v)[4], int I, bf16
 }
 
 // Integrates the replicas rep0 .. rep0 + team_replicas(D, PACK) - 1 of problem
-// a; called by all NC wavefronts of the block.
+// a; called by all wavefronts of the block.  MAP: the round-trip map of Eq. (2)
+// instead of its continuous limit: every amplitude first passes the medium
+// (A <- K(A) A, pump h = pump[replica]), then the same update runs with the
+// map's coefficients, which the host puts in eps, btil, eta and c0 (dt = 1).
 template <int D, int XS, int JS, int NC, int TW, bool PACK, bool MAP>
 __device__ __forceinline__ void integrate_team(const IntegArgs &a, int rep0, bf16x8 *lb) {
     constexpr int P = PACK ? 1 : D;                  // column planes
@@ -300,19 +320,24 @@ constexpr int team_wpe() {
     return need <= 128 ? 4 : need <= 168 ? 3 : 2;
 }
 
-// One problem: block b integrates its replicas from b * team_replicas on.
+// One problem (items = NULL): block b integrates its replicas from
+// b * team_replicas on.  Many problems of one shape: block b integrates item b,
+// (task, replica block); the host lists the longest tasks first, and the
+// hardware hands the blocks out in that order.
 template <int D, int XS, int JS, int NC, int TW, bool PACK, bool MAP, int WPE = team_wpe<D, XS, JS, NC, TW, PACK>()>
 __global__ __launch_bounds__(64 * team_waves(NC, TW)) __attribute__((amdgpu_waves_per_eu(WPE)))
-void k_integrate_team(IntegArgs a) {
+void k_integrate_team(IntegArgs one, const IntegArgs *__restrict__ tasks, const int2 *__restrict__ items) {
     extern __shared__ __align__(16) unsigned char smem[];
-    integrate_team<D, XS, JS, NC, TW, PACK, MAP>(a, blockIdx.x * team_replicas(D, PACK),
-                                                 reinterpret_cast<bf16x8 *>(smem));
+    int2 w = int2{0, (int)blockIdx.x};
+    if (items) w = items[blockIdx.x];
+    const IntegArgs a = items ? tasks[w.x] : one;
+    integrate_team<D, XS, JS, NC, TW, PACK, MAP>(a, w.y * team_replicas(D, PACK), reinterpret_cast<bf16x8 *>(smem));
 }
 
 // Largest row-tile count of the team kernels (N <= 256).
 constexpr int kTeamMaxTiles = 16;
 
-typedef void (*TeamFn)(IntegArgs);
+typedef void (*TeamFn)(IntegArgs, const IntegArgs *, const int2 *);
 
 // The plane layout's operand of all D components must fit LDS twice; D = 1
 // has the packed layout only (they coincide).

@@ -102,3 +102,33 @@ def test_coupling_reads_at_every_alignment(n, j):
     # float32 sums of n products, one rounding each for weight, update and result
     tol = (n + 4) * 2.0**-24 * (x.double().abs() + 0.01 * torch.matmul(val.abs(), x.double().abs().reshape(n, -1)).view_as(x))
     assert bool(((out.double() - ref).abs() <= tol + 1e-30).all())
+
+
+@pytest.mark.parametrize("n,d,prec,reps", [(20, 3, "f32", [5, 33]), (100, 3, "f32", [32, 7, 100]), (100, 1, "f32", [300] * 40),
+                                           (100, 3, "bf16", [500] * 9), (200, 4, "bf16", [33, 2100]), (150, 2, "f32", [40])])
+def test_batches_take_the_team_and_equal_a_chosen_kernel(n, d, prec, reps):
+    """Default plans (packed and plane layouts, ragged replica counts) against
+    a kernel chosen by the caller."""
+    J, _, _, alpha = _inputs(n, d, 1, "i8")
+    g = synth.rng(79, n, d)
+    xs = [torch.from_numpy((g.standard_normal((n, r, d)) * 0.3).astype(np.float32)).to(J.device) for r in reps]
+    pumps = [torch.from_numpy(g.uniform(0.5, 2.0, r).astype(np.float32)).to(J.device) for r in reps]
+
+    def run():
+        tasks = [dict(J=J, pump=p, x=x.clone(), alpha=alpha, eps=0.04, btil=1.0, eta=2e-4, dt=0.01, steps=STEPS - i,
+                      start_step=1, precision=prec) for i, (x, p) in enumerate(zip(xs, pumps))]
+        b = api.chym_batch_create(tasks)
+        b.launch()
+        torch.cuda.synchronize()
+        b.destroy()
+        return [t["x"] for t in tasks]
+
+    team = run()
+    slab = n > (144 if d == 2 else 128) and d > 1
+    api.chym_plan_set(n, d, prec, torch.int8, api.CHYM_KERNEL_SLAB if slab else api.CHYM_KERNEL_REGJ, 8 if slab else 4)
+    try:
+        chosen = run()
+    finally:
+        api.chym_plan_set(n, d, prec, torch.int8, api.CHYM_KERNEL_AUTO)
+    for a, b in zip(team, chosen):
+        assert _same(a, b)
