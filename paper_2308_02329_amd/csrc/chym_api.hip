@@ -158,6 +158,14 @@ int check_variant(const chym_problem *prob, const chym_run *run) {
 int slab_plan_waves(const Variant &v, int d);  // block size of the streamed-J kernel from the plan table
 bool plan_binds(const Variant &v, int d);      // a streamed-J variant's block size set by the caller
 
+// Couplings stored in eight bits, whose staging is narrow but for integers
+// that E4M3 does not hold.
+bool narrow_type(int j_dtype) { return j_dtype == CHYM_J_I8 || j_dtype == CHYM_J_FP8; }
+
+// A single problem's couplings are checked for the narrow staging formats (two
+// more launches) where the steps pay for it.
+constexpr int kNarrowSteps = 64;
+
 int integrate_impl(const chym_problem *prob, const chym_run *run, hipStream_t stream, void *ws = nullptr,
                    size_t ws_bytes = 0) {
     int rc = check_variant(prob, run);
@@ -191,8 +199,18 @@ int integrate_impl(const chym_problem *prob, const chym_run *run, hipStream_t st
         if (e != hipSuccess) return hip_fail(e, "integrate launch");
         return CHYM_OK;
     }
+    if (v.slab && !plan_binds(v, prob->d) &&
+        chym::spack_takes(v.tiles, prob->d, v.xs, v.js, narrow_type(prob->j_dtype), (run->r + pack - 1) / pack, false,
+                          cus)) {
+        hipError_t e = chym::launch_stage_jfrag(a, v.js, run->steps >= kNarrowSteps, ws, stream);
+        if (e == hipSuccess)
+            e = chym::launch_integrate_spack(v.tiles, prob->d, v.xs, v.js, (run->r + pack - 1) / pack, a, ws, nullptr,
+                                             nullptr, nullptr, stream);
+        if (e != hipSuccess) return hip_fail(e, "packed streamed-J integrate launch");
+        return CHYM_OK;
+    }
     if (v.slab) {
-        hipError_t e = chym::launch_stage_jfrag(a, v.js, ws, stream);
+        hipError_t e = chym::launch_stage_jfrag(a, v.js, false, ws, stream);
         const int waves = slab_plan_waves(v, prob->d);
         if (e == hipSuccess) e = chym::launch_integrate_slab(v.tiles, prob->d, v.xs, v.js, waves, a, ws, stream);
         if (e != hipSuccess) return hip_fail(e, "slab integrate launch");
@@ -385,6 +403,7 @@ struct Group {
     int d;
     int kind, waves;  // launch plan of this variant (resident kernels)
     int team;         // layout of the team integrator, or chym::kTeamNone
+    bool spack;       // the packed streamed-J kernel
     int item_off, n_items;
     int blocks;
     size_t lds;  // slab kernels: LDS operand area; gather kernel: the largest block's LDS
@@ -395,8 +414,8 @@ struct BatchLayout {
     std::vector<int2> items;      // (task, replica slab), grouped and sorted
     std::vector<size_t> jf_off;   // slab tasks: offset of the staged J in the workspace (else 0)
     std::vector<int> ncp;         // slab tasks: chunk count of the staging
-    std::vector<int> stage_list;  // slab tasks with one coupling term, then those with three
-    int n_stage1 = 0, n_stage3 = 0;
+    std::vector<int> stage_list;  // slab tasks: one coupling term, the same for the packed kernel, three terms
+    int n_stage1 = 0, n_stage1p = 0, n_stage3 = 0;
     size_t off_tasks, off_items, off_counters, off_score, off_first, off_jfp, off_ncp, off_list, off_jf, total;
     int64_t total_replicas;
     size_t ising_lds, hs_lds;  // scoring kernels' LDS
@@ -450,6 +469,8 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
     struct Load {
         int64_t blocks = 0, waves = 0;  // packed blocks and 16-replica groups of the team integrator
         int team = chym::kTeamNone;
+        bool spack = false;
+        bool narrow = true;  // all couplings in eight bits
     };
     std::map<GroupKey, Load> load;
     std::map<GroupKey, std::vector<int2>> by_variant;
@@ -468,6 +489,7 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         const int pack = chym::team_block_replicas(chym::kTeamPack, tk.prob.d);
         ld.blocks += (tk.run.r + pack - 1) / pack;
         ld.waves += (tk.run.r + 15) / 16;
+        ld.narrow = ld.narrow && narrow_type(tk.prob.j_dtype);
     }
     const int cus = current_cus();
     for (auto &kv : load) {
@@ -477,6 +499,9 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         if (pv.from != PlanValue::kSet)
             kv.second.team = chym::team_layout(tiles, d, xs, js, kv.second.blocks, kv.second.waves, false,
                                                pv.from == PlanValue::kTuned, cus);
+        kv.second.spack = std::get<0>(kv.first) == 1 && kv.second.team == chym::kTeamNone &&
+                          pv.from != PlanValue::kSet &&
+                          chym::spack_takes(tiles, d, xs, js, kv.second.narrow, kv.second.blocks, true, cus);
     }
     for (int t = 0; t < n_tasks; ++t) {
         const chym_task &tk = tasks[t];
@@ -489,6 +514,8 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
             slab = chym::ell_replicas_per_block(tk.prob.n, tk.prob.d);
         } else if (load[gk].team != chym::kTeamNone) {
             slab = chym::team_block_replicas(load[gk].team, tk.prob.d);
+        } else if (load[gk].spack) {
+            slab = chym::team_block_replicas(chym::kTeamPack, tk.prob.d);
         } else if (!v.slab) {
             const PlanValue pv = plan_for(key_of(v, tk.prob.d));
             slab = pv.kind != chym::kKernelRegJ ? 16 * pv.waves : 16;
@@ -514,8 +541,12 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         g.v.js = std::get<4>(kv.first);
         g.lds = 0;
         g.team = g.v.ell ? chym::kTeamNone : load[kv.first].team;
+        g.spack = !g.v.ell && load[kv.first].spack;
         if (g.team != chym::kTeamNone) {
             g.kind = -3;
+            g.waves = 0;
+        } else if (g.spack) {
+            g.kind = -4;
             g.waves = 0;
         } else if (g.v.ell) {
             g.kind = -2;
@@ -566,7 +597,7 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
     L->jf_off.assign(n_tasks, 0);
     L->ncp.assign(n_tasks, 0);
     L->stage_list.clear();
-    std::vector<int> three;
+    std::vector<int> packed, three;
     size_t off = L->off_jf;
     for (int t = 0; t < n_tasks; ++t) {
         const Variant v = variant_of(&tasks[t].prob, &tasks[t].run);
@@ -574,10 +605,12 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         L->jf_off[t] = off;
         L->ncp[t] = (v.tiles + 1) / 2;
         off += align_up(slab_ws_bytes(v));
-        (v.js == 3 ? three : L->stage_list).push_back(t);
+        (v.js == 3 ? three : load[group_of(t)].spack ? packed : L->stage_list).push_back(t);
     }
     L->n_stage1 = (int)L->stage_list.size();
+    L->n_stage1p = (int)packed.size();
     L->n_stage3 = (int)three.size();
+    L->stage_list.insert(L->stage_list.end(), packed.begin(), packed.end());
     L->stage_list.insert(L->stage_list.end(), three.begin(), three.end());
     L->total = off;
     return CHYM_OK;
@@ -611,12 +644,15 @@ int issue_batch(const chym_batch *b, hipStream_t main, const std::vector<hipStre
     int *counters = reinterpret_cast<int *>(b->ws + L.off_counters);
     hipError_t e = chym::launch_zero_counters(counters, (int)L.groups.size(), main);
     if (e != hipSuccess) return hip_fail(e, "zero counters");
-    // stage the couplings of every streamed-J task: one launch per coupling-term count
+    // stage the couplings of every streamed-J task: the slab kernel's, the packed kernel's, three terms
     const int *list_d = reinterpret_cast<const int *>(b->ws + L.off_list);
     const int *ncp_d = reinterpret_cast<const int *>(b->ws + L.off_ncp);
     unsigned char *const *jfp_d = reinterpret_cast<unsigned char *const *>(b->ws + L.off_jfp);
-    e = chym::launch_stage_batched(1, tasks_d, list_d, L.n_stage1, ncp_d, jfp_d, main);
-    if (e == hipSuccess) e = chym::launch_stage_batched(3, tasks_d, list_d + L.n_stage1, L.n_stage3, ncp_d, jfp_d, main);
+    e = chym::launch_stage_batched(1, false, tasks_d, list_d, L.n_stage1, ncp_d, jfp_d, main);
+    list_d += L.n_stage1;
+    if (e == hipSuccess) e = chym::launch_stage_batched(1, true, tasks_d, list_d, L.n_stage1p, ncp_d, jfp_d, main);
+    list_d += L.n_stage1p;
+    if (e == hipSuccess) e = chym::launch_stage_batched(3, false, tasks_d, list_d, L.n_stage3, ncp_d, jfp_d, main);
     if (e != hipSuccess) return hip_fail(e, "stage J");
     const bool fork = branches && L.groups.size() > 1;
     if (fork) {
@@ -633,6 +669,10 @@ int issue_batch(const chym_batch *b, hipStream_t main, const std::vector<hipStre
         if (g.team != chym::kTeamNone)
             e = chym::launch_integrate_team(g.team, g.v.tiles, g.d, g.v.xs, g.v.js, false, g.n_items, chym::IntegArgs{},
                                             tasks_d, items_d + g.item_off, s);
+        else if (g.spack)
+            e = chym::launch_integrate_spack(g.v.tiles, g.d, g.v.xs, g.v.js, g.n_items, chym::IntegArgs{}, nullptr,
+                                             tasks_d, items_d + g.item_off,
+                                             reinterpret_cast<const void *const *>(b->ws + L.off_jfp), s);
         else if (g.v.ell)
             e = chym::launch_integrate_ell_persistent(g.d, g.blocks, g.lds, tasks_d, items_d + g.item_off, g.n_items,
                                                       counters + gi, s);
@@ -806,7 +846,7 @@ int batch_build(const chym_task *tasks, int32_t n_tasks, void *workspace, size_t
     b->cus = cus;
     for (Group &g : b->layout.groups) {
         int per_cu = 0;
-        if (e == hipSuccess && g.team == chym::kTeamNone) {
+        if (e == hipSuccess && g.team == chym::kTeamNone && !g.spack) {
             if (g.v.ell) e = chym::ell_persistent_occupancy(g.d, g.lds, &per_cu);
             else if (g.v.slab) e = chym::slab_occupancy(g.v.tiles, g.d, g.v.xs, g.v.js, g.waves, g.lds, &per_cu);
             else e = chym::persistent_occupancy(g.v.tiles, g.d, g.v.xs, g.v.js, g.kind, g.waves, &per_cu);

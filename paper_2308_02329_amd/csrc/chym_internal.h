@@ -261,11 +261,13 @@ size_t slab_lds_bytes(int tiles, int d, int xs);
 size_t slab_jfrag_bytes(int tiles, int js);
 bool slab_variant_exists(int tiles, int d, int xs, int js);  // the eight-wavefront shape
 bool slab_shape_exists(int tiles, int d, int xs, int js, int waves);
-hipError_t launch_stage_jfrag(const IntegArgs &a, int js, void *out, hipStream_t stream);
+// narrow: couplings in one term may be staged as E2M1 or E4M3 codes (else
+// bf16), in quads, for the packed streamed-J integrator.
+hipError_t launch_stage_jfrag(const IntegArgs &a, int js, bool narrow, void *out, hipStream_t stream);
 // Stages the couplings of the tasks list[0 .. n) of a batch (all with js
-// coupling terms) into stages[task], ncps[task] chunks each; tasks, list,
-// ncps and stages are device arrays.
-hipError_t launch_stage_batched(int js, const IntegArgs *tasks, const int *list, int n, const int *ncps,
+// coupling terms) into stages[task], ncps[task] chunks each, narrow ones in
+// quads or not; tasks, list, ncps and stages are device arrays.
+hipError_t launch_stage_batched(int js, bool quads, const IntegArgs *tasks, const int *list, int n, const int *ncps,
                                 unsigned char *const *stages, hipStream_t stream);
 hipError_t launch_integrate_slab(int tiles, int d, int xs, int js, int waves, const IntegArgs &a, const void *jfrag,
                                  hipStream_t stream);
@@ -273,6 +275,15 @@ hipError_t slab_occupancy(int tiles, int d, int xs, int js, int waves, size_t ld
 hipError_t launch_integrate_slab_persistent(int tiles, int d, int xs, int js, int waves, size_t lds, int blocks,
                                             const IntegArgs *tasks, const int2 *items, int n_items, int *counter,
                                             const void *const *jfs, const int *ncps, hipStream_t stream);
+
+// Packed streamed-J integrator (16 columns per block), for launches of few
+// replicas: whether it takes `blocks` packed blocks on cus compute units
+// (narrow: the couplings are stored in eight bits; batch: in one batch group),
+// and its launch (one problem staged at `stage`, or items of many problems).
+bool spack_takes(int tiles, int d, int xs, int js, bool narrow, int64_t blocks, bool batch, int cus);
+hipError_t launch_integrate_spack(int tiles, int d, int xs, int js, int blocks, const IntegArgs &one,
+                                  const void *stage, const IntegArgs *tasks, const int2 *items,
+                                  const void *const *stages, hipStream_t stream);
 
 // Learned early restart: trajectory features and the MLP.
 hipError_t launch_features(int n, int d, int r, const void *j, int j_dtype, const float *x, uint64_t *prev,

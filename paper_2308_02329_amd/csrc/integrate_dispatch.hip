@@ -1,6 +1,6 @@
 // Host-side dispatch of the register-resident integrator variants.
 #include "integrate_slab.h"
-#include "integrate_team.h"
+#include "integrate_spack.h"
 
 namespace chym {
 
@@ -78,104 +78,115 @@ bool slab_shape_exists(int tiles, int d, int xs, int js, int waves) {
 // Decides the staging format of the couplings, checked element by element:
 // E2M1 codes when every coupling is -1, 0 or +1; else E4M3 bytes when every
 // row is a set of E4M3 values times one power of two (the row scale, chosen
-// as in the FP8 quantizer; FP8 storage always qualifies); else bf16.
-// Writes the header and the row scales.  Run by one block of 1024 threads:
-// wavefront w takes rows w, w + 16, ...  (Batches only: a single problem's
-// staging is always bf16, k_stage_bf16_header.)
-__device__ __forceinline__ void stage_prep_block(const IntegArgs &a, int tiles, unsigned char *__restrict__ stage) {
-    __shared__ int s_ok, s_pm1;
-    if (threadIdx.x == 0) {
-        s_ok = 1;
-        s_pm1 = 1;
-    }
-    __syncthreads();
+// as in the FP8 quantizer; FP8 storage always qualifies); else bf16.  A launch
+// sets the header's flags, then blocks of four rows, one per wavefront, clear
+// them and write the row scales.  (One block per task that walked all its rows
+// took 586 us for 75 tasks of N = 50 - 800; now 17 us.)
+__device__ __forceinline__ void stage_prep_row(const IntegArgs &a, int p, unsigned char *__restrict__ stage) {
+    int *flags = reinterpret_cast<int *>(stage);
     float *scale = reinterpret_cast<float *>(stage + kStageHeader);
     const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
     const int n = a.n;
     bool ok = true, pm1 = true;
-    for (int p = w; p < tiles * 16; p += 16) {
-        float sc = 1.0f;
-        if (p < n) {
-            if (a.j_dtype == CHYM_J_FP8) {
-                const uint32_t e = reinterpret_cast<const uint8_t *>(a.j)[(size_t)n * n + p];
-                sc = e == 0xffu ? __builtin_nanf("") : ldexpf(1.0f, (int)e - 127);
-                for (int q = lane; q < n; q += 64) {
-                    const float v = coupling(a.j, a.j_dtype, n, p, q);
-                    if (!(v == 0.0f || v == 1.0f || v == -1.0f)) pm1 = false;
-                }
+    float sc = 1.0f;
+    if (p < n) {
+        if (a.j_dtype == CHYM_J_FP8) {
+            const uint32_t e = reinterpret_cast<const uint8_t *>(a.j)[(size_t)n * n + p];
+            sc = e == 0xffu ? __builtin_nanf("") : ldexpf(1.0f, (int)e - 127);
+            for (int q = lane; q < n; q += 64) {
+                const float v = coupling(a.j, a.j_dtype, n, p, q);
+                if (!(v == 0.0f || v == 1.0f || v == -1.0f)) pm1 = false;
+            }
+        } else {
+            float amax = 0.0f;
+            bool fin = true;
+            for (int q = lane; q < n; q += 64) {
+                const float v = coupling(a.j, a.j_dtype, n, p, q);
+                fin = fin && __builtin_isfinite(v);
+                amax = fmaxf(amax, fabsf(v));
+                if (!(v == 0.0f || v == 1.0f || v == -1.0f)) pm1 = false;
+            }
+            for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+            const int e = e4m3_row_exponent(amax);
+            if (!__all(fin) || e < -126 || e > 127) {
+                ok = false;
             } else {
-                float amax = 0.0f;
-                bool fin = true;
+                sc = ldexpf(1.0f, e);
                 for (int q = lane; q < n; q += 64) {
                     const float v = coupling(a.j, a.j_dtype, n, p, q);
-                    fin = fin && __builtin_isfinite(v);
-                    amax = fmaxf(amax, fabsf(v));
-                    if (!(v == 0.0f || v == 1.0f || v == -1.0f)) pm1 = false;
-                }
-                for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
-                const int e = e4m3_row_exponent(amax);
-                if (!__all(fin) || e < -126 || e > 127) {
-                    ok = false;
-                } else {
-                    sc = ldexpf(1.0f, e);
-                    for (int q = lane; q < n; q += 64) {
-                        const float v = coupling(a.j, a.j_dtype, n, p, q);
-                        if (ldexpf(e4m3_value(e4m3_code(ldexpf(v, -e))), e) != v) ok = false;
-                    }
+                    if (ldexpf(e4m3_value(e4m3_code(ldexpf(v, -e))), e) != v) ok = false;
                 }
             }
         }
-        if (lane == 0) scale[p] = sc;
     }
-    if (!ok) atomicAnd(&s_ok, 0);
-    if (!pm1) atomicAnd(&s_pm1, 0);
-    __syncthreads();
-    if (threadIdx.x == 0)
-        *reinterpret_cast<int *>(stage) = s_pm1 ? kStageE2M1
-                                                : ((a.j_dtype == CHYM_J_FP8 || s_ok) ? kStageE4M3 : kStageBf16);
+    ok = __all(ok);
+    pm1 = __all(pm1);
+    if (lane == 0) {
+        scale[p] = sc;
+        if (!pm1) atomicAnd(&flags[0], 0);
+        if (!ok) atomicAnd(&flags[1], 0);
+    }
 }
 
-// A single problem's staging header: bf16 fragments.
-__global__ void k_stage_bf16_header(unsigned char *__restrict__ stage) {
-    if (threadIdx.x == 0) *reinterpret_cast<int *>(stage) = kStageBf16;
+// Header flags of n stagings: both set (the row pass clears what does not
+// hold), or both clear (bf16 fragments).
+__global__ void k_stage_header(const int *__restrict__ list, int n, unsigned char *const *__restrict__ stages,
+                               unsigned char *__restrict__ one, int value) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    int *flags = reinterpret_cast<int *>(one ? one : stages[list[i]]);
+    flags[0] = value;
+    flags[1] = value;
 }
 
-// The same for the tasks list[0 .. n) of a batch, one block each.
-__global__ __launch_bounds__(1024) void k_stage_prep_batched(const IntegArgs *__restrict__ tasks,
-                                                             const int *__restrict__ list,
-                                                             unsigned char *const *__restrict__ stages) {
-    const int t = list[blockIdx.x];
+__global__ __launch_bounds__(256) void k_stage_prep(IntegArgs a, unsigned char *__restrict__ stage) {
+    const int p = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (p < (a.n + 15) / 16 * 16) stage_prep_row(a, p, stage);
+}
+
+// The same for the tasks list[0 .. n) of a batch, bpt blocks each.
+__global__ __launch_bounds__(256) void k_stage_prep_batched(const IntegArgs *__restrict__ tasks,
+                                                            const int *__restrict__ list, int bpt,
+                                                            unsigned char *const *__restrict__ stages) {
+    const int t = list[blockIdx.x / bpt];
     const IntegArgs a = tasks[t];
-    stage_prep_block(a, (a.n + 15) / 16, stages[t]);
+    const int rows = (a.n + 15) / 16 * 16;
+    for (int p = (blockIdx.x % bpt) * 4 + (threadIdx.x >> 6); p < rows; p += 4 * bpt) stage_prep_row(a, p, stages[t]);
 }
 
-hipError_t launch_stage_batched(int js, const IntegArgs *tasks, const int *list, int n, const int *ncps,
+constexpr int kStageBlocksPerTask = 32;  // 128 rows at a time; 8192 threads share a task's fragment slots
+
+hipError_t launch_stage_batched(int js, bool quads, const IntegArgs *tasks, const int *list, int n, const int *ncps,
                                 unsigned char *const *stages, hipStream_t stream) {
     if (n <= 0) return hipSuccess;
-    constexpr int kBlocksPerTask = 32;  // 8192 threads share a task's fragment slots
     if (js == 3) {
-        hipLaunchKernelGGL(k_stage_jfrag_batched<3>, dim3(n * kBlocksPerTask), dim3(256), 0, stream, tasks, list,
-                           kBlocksPerTask, ncps, stages);
+        hipLaunchKernelGGL(k_stage_jfrag_batched<3>, dim3(n * kStageBlocksPerTask), dim3(256), 0, stream, tasks, list,
+                           kStageBlocksPerTask, ncps, quads, stages);
     } else {
-        hipLaunchKernelGGL(k_stage_prep_batched, dim3(n), dim3(1024), 0, stream, tasks, list, stages);
-        hipLaunchKernelGGL(k_stage_jfrag_batched<1>, dim3(n * kBlocksPerTask), dim3(256), 0, stream, tasks, list,
-                           kBlocksPerTask, ncps, stages);
+        hipLaunchKernelGGL(k_stage_header, dim3((n + 255) / 256), dim3(256), 0, stream, list, n, stages,
+                           (unsigned char *)nullptr, 1);
+        hipLaunchKernelGGL(k_stage_prep_batched, dim3(n * kStageBlocksPerTask), dim3(256), 0, stream, tasks, list,
+                           kStageBlocksPerTask, stages);
+        hipLaunchKernelGGL(k_stage_jfrag_batched<1>, dim3(n * kStageBlocksPerTask), dim3(256), 0, stream, tasks, list,
+                           kStageBlocksPerTask, ncps, quads, stages);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_stage_jfrag(const IntegArgs &a, int js, void *out, hipStream_t stream) {
+hipError_t launch_stage_jfrag(const IntegArgs &a, int js, bool narrow, void *out, hipStream_t stream) {
+    const bool quads = narrow;  // the packed kernel alone takes the narrow formats of a single problem
     const int nt = (a.n + 15) / 16;
     const int ncp = (nt + 1) / 2;
     const int total = nt * ncp * 64;
     const int grid = (total + 255) / 256;
     unsigned char *stage = reinterpret_cast<unsigned char *>(out);
     if (js == 3) {
-        hipLaunchKernelGGL(k_stage_jfrag<3>, dim3(grid), dim3(256), 0, stream, a, ncp, stage);
+        hipLaunchKernelGGL(k_stage_jfrag<3>, dim3(grid), dim3(256), 0, stream, a, ncp, quads, stage);
     } else {
-        hipLaunchKernelGGL(k_stage_bf16_header, dim3(1), dim3(64), 0, stream, stage);
-        hipLaunchKernelGGL(k_stage_jfrag<1>, dim3(grid), dim3(256), 0, stream, a, ncp, stage);
+        hipLaunchKernelGGL(k_stage_header, dim3(1), dim3(64), 0, stream, (const int *)nullptr, 1,
+                           (unsigned char *const *)nullptr, stage, narrow ? 1 : 0);
+        if (narrow) hipLaunchKernelGGL(k_stage_prep, dim3(nt * 4), dim3(256), 0, stream, a, stage);
+        hipLaunchKernelGGL(k_stage_jfrag<1>, dim3(grid), dim3(256), 0, stream, a, ncp, quads, stage);
     }
     return hipGetLastError();
 }
@@ -291,6 +302,61 @@ hipError_t launch_integrate_team(int layout, int tiles, int d, int xs, int js, b
     }
     hipLaunchKernelGGL(fn, dim3(blocks), dim3(64 * team_waves(nc, team_tiles(tiles, xs, pack))), lds, stream, one, tasks,
                        items);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------- packed streamed-J kernels
+static SpackFn lookup_spack(int tiles, int d, int xs, int js) {
+    switch (d) {
+        case 1: return lookup_spack_1(tiles, xs, js);
+        case 2: return lookup_spack_2(tiles, xs, js);
+        case 3: return lookup_spack_3(tiles, xs, js);
+        case 4: return lookup_spack_4(tiles, xs, js);
+        default: return nullptr;
+    }
+}
+
+// Where the packed kernel is faster than the slab kernel (one problem, slab
+// time / packed time, at N = 260, 512, 800, 1000; +-1 couplings are "narrow"):
+//                                packed blocks per CU    0.25 - 1            2
+//   three state terms, D = 4, narrow          1.9 - 2.1, 3.9 - 4.5,    1.0, 2.1,
+//                                             3.6 - 4.5, 3.9 - 5.0     1.9, 2.1
+//   the same, D = 2                           1.4 - 1.6, 1.6 - 1.7,    0.8, 0.9,
+//                                             1.6 - 1.8, 2.0 - 2.2     0.9, 1.1
+//   three coupling terms, D = 4               1.3 - 1.6, 2.9 - 3.7,    0.7, 1.5,
+//                                             2.4 - 3.2, 3.3 - 4.2     1.3, 1.7
+//   the same, D = 1                           1.0 - 1.1, 1.0, 0.9 - 1.0, 0.9 - 1.0
+//   one state term, D = 4, narrow             1.0 - 1.1, 1.8 - 2.0,    0.7, 1.1,
+//                                             1.6 - 1.8, 2.0 - 2.3     0.9, 1.1
+//   the same, bf16 couplings                  0.8, 1.1 - 1.2, 1.0 - 1.1, 1.0 - 1.3
+//   the same, D = 1                           0.95, 1.0, 1.0, 0.95
+// A block streams all of J either way, so with D = 1 or one state term, where
+// the slab's products are no more than that stream costs, only narrow
+// couplings gain.  Up to three blocks per CU, one after another, pay where the
+// slab kernel passes over J once per component (three state terms, D >= 3,
+// more than 32 tiles).
+bool spack_takes(int tiles, int d, int xs, int js, bool narrow, int64_t blocks, bool batch, int cus) {
+    if (!lookup_spack(tiles, d, xs, js)) return false;
+    if (blocks > cus) {
+        if (batch || xs != 3 || d < 3 || tiles <= 32) return false;
+        return blocks <= (d == 4 && js == 1 ? 3 : 2) * (int64_t)cus;
+    }
+    if (js == 3) return d > 1;
+    if (narrow) return xs == 3 || d < 3 || tiles >= 24;
+    return xs == 3 ? d > 1 : d == 4 && tiles >= 24 && 2 * blocks <= cus;
+}
+
+hipError_t launch_integrate_spack(int tiles, int d, int xs, int js, int blocks, const IntegArgs &one,
+                                  const void *stage, const IntegArgs *tasks, const int2 *items,
+                                  const void *const *stages, hipStream_t stream) {
+    SpackFn fn = lookup_spack(tiles, d, xs, js);
+    if (!fn) return hipErrorInvalidDeviceFunction;
+    const size_t lds = spack_lds_bytes((tiles + 1) / 2, xs);
+    hipError_t e = slab_prepare(reinterpret_cast<const void *>(fn), lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(64 * kSpackWaves), lds, stream, one,
+                       reinterpret_cast<const unsigned char *>(stage), tasks, items,
+                       reinterpret_cast<const unsigned char *const *>(stages));
     return hipGetLastError();
 }
 

@@ -50,15 +50,27 @@
 namespace chym {
 
 // Staged couplings of one problem (caller workspace, 256-byte aligned):
-//   [0, 256)           header: int32 format, kStageBf16, kStageE4M3 or kStageE2M1
+//   [0, 256)           header: two int32 flags, whether every coupling is in
+//                      {-1, 0, +1} and whether every row is E4M3 values times
+//                      one power of two; they give the fragments' format
 //   [256, 256 + S)     float row scales 2^e_p [tiles * 16] (E4M3 fragments)
 //   [256 + S, ...)     fragments: bf16 [tile][chunk][JS][64 lanes] x 16 B,
 //                      E4M3 [tile][chunk][64 lanes] x 8 B, or
-//                      E2M1 [tile][chunk][64 lanes] x 4 B
+//                      E2M1 [tile][chunk][64 lanes] x 4 B; for the packed
+//                      kernel, whose lanes load 16 B each time, the narrow ones
+//                      are [tile][quad][64 lanes][chunk of the quad], two E4M3
+//                      or four E2M1 chunks to the quad
 constexpr size_t kStageHeader = 256;
 constexpr int kStageBf16 = 0;
 constexpr int kStageE4M3 = 1;
 constexpr int kStageE2M1 = 2;  // couplings in {-1, 0, +1}
+// The format by the header's flags (uniform; written before the fragments are).
+__device__ __forceinline__ int stage_format(const unsigned char *stage) {
+    const int *h = reinterpret_cast<const int *>(stage);
+    return h[0] ? kStageE2M1 : (h[1] ? kStageE4M3 : kStageBf16);
+}
+// chunks in one 16-byte load of a lane
+__host__ __device__ constexpr int stage_quad_chunks(int fmt) { return fmt == kStageE2M1 ? 4 : fmt == kStageE4M3 ? 2 : 1; }
 // the most chunks of J fragments the streamed-J kernel keeps in flight (its
 // prefetch ring); the staging carries that many chunks of padding after the
 // last tile
@@ -461,23 +473,26 @@ __device__ __forceinline__ void integrate_slab(const IntegArgs &a, int rep0, con
 }
 
 // Stages J of one problem as A fragments: bf16 [tile][chunk][JS][64 lanes],
-// or (JS = 1 and the header flag set) E4M3 [tile][chunk][64 lanes] in the
-// same slot order.  Threads first, first + stride, ... of the launch share
+// or (JS = 1, by the header's flags) E4M3 or E2M1 [tile][chunk][64 lanes] in
+// the same slot order, or in quads of chunks.  Threads first, first + stride, ... of the launch share
 // the fragment slots.
 template <int JS>
 __device__ __forceinline__ void stage_jfrag_part(const IntegArgs &a, int ncp, unsigned char *__restrict__ stage,
-                                                 int first, int stride) {
+                                                 bool quads, int first, int stride) {
     const int nt = (a.n + 15) / 16;
     const int total = nt * ncp * 64;
-    const int fmt = JS == 1 ? *reinterpret_cast<const int *>(stage) : kStageBf16;
+    const int fmt = JS == 1 ? stage_format(stage) : kStageBf16;
     const float *scale = reinterpret_cast<const float *>(stage + kStageHeader);
     bf16x8 *out = reinterpret_cast<bf16x8 *>(stage + stage_frag_offset(nt));
     uint2 *out8 = reinterpret_cast<uint2 *>(stage + stage_frag_offset(nt));
     uint32_t *out4 = reinterpret_cast<uint32_t *>(stage + stage_frag_offset(nt));
+    const int cpq = quads ? stage_quad_chunks(fmt) : 1;
+    const int ncq = (ncp + cpq - 1) / cpq;
     for (int idx = first; idx < total; idx += stride) {
         const int lane = idx & 63;
         const int c = (idx >> 6) % ncp;
         const int I = (idx >> 6) / ncp;
+        const size_t slot = ((size_t)(I * ncq + c / cpq) * 64 + lane) * cpq + c % cpq;
         if (fmt == kStageE2M1) {
             // every coupling is -1, 0 or +1: E2M1 codes 0xA, 0x0, 0x2
             const int i = lane & 15, g = lane >> 4;
@@ -490,7 +505,7 @@ __device__ __forceinline__ void stage_jfrag_part(const IntegArgs &a, int ncp, un
                 const uint32_t code = v > 0.0f ? 0x2u : (v < 0.0f ? 0xAu : 0x0u);
                 wd |= code << (4 * s);
             }
-            out4[(size_t)(I * ncp + c) * 64 + lane] = wd;
+            out4[slot] = wd;
         } else if (fmt == kStageE4M3) {
             const int i = lane & 15, g = lane >> 4;
             const int p = 16 * I + i;
@@ -506,7 +521,7 @@ __device__ __forceinline__ void stage_jfrag_part(const IntegArgs &a, int ncp, un
                 }
                 wd[s >> 2] |= code << (8 * (s & 3));
             }
-            out8[(size_t)(I * ncp + c) * 64 + lane] = uint2{wd[0], wd[1]};
+            out8[slot] = uint2{wd[0], wd[1]};
         } else {
             bf16x8 f[JS];
             j_fragment<JS>(a, I, c, lane, f);
@@ -517,8 +532,9 @@ __device__ __forceinline__ void stage_jfrag_part(const IntegArgs &a, int ncp, un
 }
 
 template <int JS>
-__global__ __launch_bounds__(256) void k_stage_jfrag(IntegArgs a, int ncp, unsigned char *__restrict__ stage) {
-    stage_jfrag_part<JS>(a, ncp, stage, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+__global__ __launch_bounds__(256) void k_stage_jfrag(IntegArgs a, int ncp, bool quads,
+                                                     unsigned char *__restrict__ stage) {
+    stage_jfrag_part<JS>(a, ncp, stage, quads, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
 // The same for the tasks list[0 .. n) of a batch, bpt blocks per task:
@@ -526,11 +542,11 @@ __global__ __launch_bounds__(256) void k_stage_jfrag(IntegArgs a, int ncp, unsig
 template <int JS>
 __global__ __launch_bounds__(256) void k_stage_jfrag_batched(const IntegArgs *__restrict__ tasks,
                                                              const int *__restrict__ list, int bpt,
-                                                             const int *__restrict__ ncps,
+                                                             const int *__restrict__ ncps, bool quads,
                                                              unsigned char *const *__restrict__ stages) {
     const int t = list[blockIdx.x / bpt];
     const IntegArgs a = tasks[t];
-    stage_jfrag_part<JS>(a, ncps[t], stages[t], (blockIdx.x % bpt) * blockDim.x + threadIdx.x, bpt * blockDim.x);
+    stage_jfrag_part<JS>(a, ncps[t], stages[t], quads, (blockIdx.x % bpt) * blockDim.x + threadIdx.x, bpt * blockDim.x);
 }
 
 // The narrow formats exist for single-term couplings; the header is uniform.
@@ -538,7 +554,7 @@ template <int D, int XS, int JS, int TPW, int W, bool CP>
 __device__ __forceinline__ void slab_run(const IntegArgs &a, int rep0, const unsigned char *stage, int ncp,
                                          bf16x8 *lb) {
     if constexpr (JS == 1) {
-        const int fmt = __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int *>(stage));
+        const int fmt = __builtin_amdgcn_readfirstlane(stage_format(stage));
         if (fmt == kStageE2M1) {
             integrate_slab<D, XS, JS, TPW, kStageE2M1, W, 2, CP>(a, rep0, stage, ncp, lb);
             return;
