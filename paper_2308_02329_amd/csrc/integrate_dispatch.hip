@@ -149,9 +149,9 @@ __global__ __launch_bounds__(256) void k_stage_prep_batched(const IntegArgs *__r
                                                             const int *__restrict__ list, int bpt,
                                                             unsigned char *const *__restrict__ stages) {
     const int t = list[blockIdx.x / bpt];
-    const IntegArgs a = tasks[t];
+    const IntegArgs a = in_wave(tasks[t]);
     const int rows = (a.n + 15) / 16 * 16;
-    for (int p = (blockIdx.x % bpt) * 4 + (threadIdx.x >> 6); p < rows; p += 4 * bpt) stage_prep_row(a, p, stages[t]);
+    for (int p = (blockIdx.x % bpt) * 4 + (threadIdx.x >> 6); p < rows; p += 4 * bpt) stage_prep_row(a, p, in_wave(stages[t]));
 }
 
 constexpr int kStageBlocksPerTask = 32;  // 128 rows at a time; 8192 threads share a task's fragment slots

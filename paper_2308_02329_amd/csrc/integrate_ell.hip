@@ -276,7 +276,7 @@ __global__ __launch_bounds__(kEllThreads) void k_integrate_ell_persistent(const 
         const int it = s_item;
         if (it >= n_items) break;
         const int2 w = items[it];
-        const IntegArgs a = tasks[w.x];
+        const IntegArgs a = in_wave(tasks[w.x]);
         const int lrb = ell_log2(ell_rb(a.n, D));
         ell_block<D>(a, w.y << lrb, lrb, sm);
     }

@@ -384,7 +384,7 @@ __global__ __launch_bounds__(256) void k_integrate_persistent(const IntegArgs *_
         it = __builtin_amdgcn_readfirstlane(__shfl(it, 0, 64));
         if (it >= n_items) break;
         const int2 w = items[it];
-        const IntegArgs a = tasks[w.x];
+        const IntegArgs a = in_wave(tasks[w.x]);
         integrate_group<NT, D, XS, JS, false>(a, w.y * 16, nullptr);
     }
 }
@@ -412,7 +412,7 @@ void k_integrate_persistent_lds(const IntegArgs *__restrict__ tasks, const int2 
         const int it = __builtin_amdgcn_readfirstlane(s_item);
         if (it >= n_items) break;
         const int2 w = items[it];
-        const IntegArgs a = tasks[w.x];
+        const IntegArgs a = in_wave(tasks[w.x]);
         stage_j<NT, JS>(a, jl);
         __syncthreads();
         const int rep0 = (w.y * waves + wave) * 16;
@@ -647,7 +647,7 @@ void k_integrate_persistent_pipe(const IntegArgs *__restrict__ tasks, const int2
         const int it = __builtin_amdgcn_readfirstlane(s_item);
         if (it >= n_items) break;
         const int2 w = items[it];
-        const IntegArgs a = tasks[w.x];
+        const IntegArgs a = in_wave(tasks[w.x]);
         stage_j<NT, JS>(a, jl);
         __syncthreads();
         const int rep0 = (w.y * waves + wave) * 16;

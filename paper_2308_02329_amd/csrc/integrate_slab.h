@@ -545,8 +545,8 @@ __global__ __launch_bounds__(256) void k_stage_jfrag_batched(const IntegArgs *__
                                                              const int *__restrict__ ncps, bool quads,
                                                              unsigned char *const *__restrict__ stages) {
     const int t = list[blockIdx.x / bpt];
-    const IntegArgs a = tasks[t];
-    stage_jfrag_part<JS>(a, ncps[t], stages[t], quads, (blockIdx.x % bpt) * blockDim.x + threadIdx.x, bpt * blockDim.x);
+    const IntegArgs a = in_wave(tasks[t]);
+    stage_jfrag_part<JS>(a, ncps[t], in_wave(stages[t]), quads, (blockIdx.x % bpt) * blockDim.x + threadIdx.x, bpt * blockDim.x);
 }
 
 // The narrow formats exist for single-term couplings; the header is uniform.
@@ -601,8 +601,8 @@ void k_integrate_slab_persistent(const IntegArgs *__restrict__ tasks, const int2
         const int it = __builtin_amdgcn_readfirstlane(s_item);
         if (it >= n_items) break;
         const int2 wi = items[it];
-        const IntegArgs a = tasks[wi.x];
-        slab_run<D, XS, JS, TPW, W, CP>(a, wi.y * 16, jfs[wi.x], ncps[wi.x], reinterpret_cast<bf16x8 *>(smem));
+        const IntegArgs a = in_wave(tasks[wi.x]);
+        slab_run<D, XS, JS, TPW, W, CP>(a, wi.y * 16, in_wave(jfs[wi.x]), ncps[wi.x], reinterpret_cast<bf16x8 *>(smem));
     }
 }
 

@@ -176,11 +176,7 @@ __device__ __forceinline__ void integrate_spack(const IntegArgs &a, int rep0, co
                 }
             };
             // The next quad (past the end, the next group's or step's first) is
-            // loaded while this one is used, and moved into its place after: the
-            // moves cost 8 instructions per tile and eight or more products, a
-            // ring of several quads waits for all its loads at the loop's head,
-            // which the tail's refills reach in another order (N = 800, one
-            // state term, E2M1: 7.0 us per step, 9.0 with a ring of four).
+            // loaded while this one is used, and moved into its place after.
             i4 nxt[GS][JS];
             int cq = 0;
             for (; (cq + 1) * CPQ <= ncp; ++cq) {
@@ -243,8 +239,8 @@ void k_integrate_spack(IntegArgs one, const unsigned char *__restrict__ stage0, 
     bf16x8 *lb = reinterpret_cast<bf16x8 *>(smem);
     int2 wi = int2{0, (int)blockIdx.x};
     if (items) wi = items[blockIdx.x];
-    const IntegArgs a = items ? tasks[wi.x] : one;
-    const unsigned char *stage = items ? stages[wi.x] : stage0;
+    const IntegArgs a = in_wave(items ? tasks[wi.x] : one);
+    const unsigned char *stage = in_wave(items ? stages[wi.x] : stage0);
     const int ncp = ((a.n + 15) / 16 + 1) / 2;
     const int rep0 = wi.y * team_replicas(D, true);
     if constexpr (JS == 1) {

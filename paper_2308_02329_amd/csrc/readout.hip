@@ -93,7 +93,7 @@ __device__ __forceinline__ void readout_block(int n, int r, int rep, bool mine, 
     }
 }
 
-__device__ void readout_any(int n, int d, int r, int rep, bool mine, int nw, const float *__restrict__ x,
+__device__ __forceinline__ void readout_any(int n, int d, int r, int rep, bool mine, int nw, const float *__restrict__ x,
                             uint64_t *__restrict__ spins, double *__restrict__ extra,
                             uint8_t *__restrict__ diverged, ReadoutLds &sm) {
     switch (d) {
@@ -187,7 +187,7 @@ __device__ __forceinline__ i32x4 int8_row16(const int8_t *__restrict__ J, int n,
 // rows that this replaces was bound by its chain of row reads (N = 200, 20000
 // replicas: 180 us; now 16 us).  Called by all threads of the block; contains
 // block barriers.
-__device__ void ising_block_i8(int n, int rep0, int cnt, const int8_t *__restrict__ J,
+__device__ __forceinline__ void ising_block_i8(int n, int rep0, int cnt, const int8_t *__restrict__ J,
                                const uint64_t *__restrict__ spins, int32_t *__restrict__ e_i32,
                                double *__restrict__ e_f64, int (&red)[4][16]) {
     const int lane = threadIdx.x & 63;
@@ -255,7 +255,7 @@ __device__ __forceinline__ int quad_row(int p) { return p * 16 + (p >> 2) * 8; }
 
 size_t quad_lds_bytes(int n) { return sizeof(double) * (size_t)((n + 15) / 16) * 16 * 18; }
 
-__device__ void quad_block(int n, int d, int r, int rep0, int cnt, const void *__restrict__ j, int j_dtype,
+__device__ __forceinline__ void quad_block(int n, int d, int r, int rep0, int cnt, const void *__restrict__ j, int j_dtype,
                            const float *__restrict__ x, const uint64_t *__restrict__ spins, double *__restrict__ out,
                            double *u, double (&red)[4][16]) {
     const int lane = threadIdx.x & 63;
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(1024) void k_readout_batched(const ScoreArgs *__res
         const int64_t b1 = min(b0 + 64, total);
         const int64_t g = b0 + (threadIdx.x & 63);
         for (int k = task_of(first, n_tasks, b0); k < n_tasks && first[k] < b1; ++k) {
-            const ScoreArgs &a = t[k];
+            const ScoreArgs a = in_wave(t[k]);
             if (first[k + 1] <= b0 || first[k + 1] == first[k] || (!a.spins && !a.extra && !a.diverged)) continue;
             const bool mine = g >= first[k] && g < first[k + 1] && g < b1;
             readout_any(a.n, a.d, a.r, mine ? (int)(g - first[k]) : 0, mine, blockDim.x >> 6, a.x, a.spins, a.extra,
@@ -477,7 +477,7 @@ __global__ __launch_bounds__(kEnergyThreads) void k_ising_batched(const ScoreArg
          b0 += (int64_t)gridDim.x * kIsingBlockReplicas) {
         const int64_t b1 = min(b0 + kIsingBlockReplicas, total);
         for (int k = task_of(first, n_tasks, b0); k < n_tasks && first[k] < b1; ++k) {
-            const ScoreArgs &a = t[k];
+            const ScoreArgs a = in_wave(t[k]);
             if (!a.e_i32 && !a.e_f64) continue;
             const int64_t s0 = max(first[k], b0), s1 = min(first[k + 1], b1);
             if (s1 <= s0) continue;
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(kEnergyThreads) void k_hs_batched(const ScoreArgs *
     for (int64_t b0 = (int64_t)blockIdx.x * kHsBlockReplicas; b0 < total; b0 += (int64_t)gridDim.x * kHsBlockReplicas) {
         const int64_t b1 = min(b0 + kHsBlockReplicas, total);
         for (int k = task_of(first, n_tasks, b0); k < n_tasks && first[k] < b1; ++k) {
-            const ScoreArgs &a = t[k];
+            const ScoreArgs a = in_wave(t[k]);
             if (!a.e_hs) continue;
             const int64_t s0 = max(first[k], b0), s1 = min(first[k + 1], b1);
             if (s1 <= s0) continue;
