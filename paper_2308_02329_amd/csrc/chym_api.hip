@@ -204,8 +204,7 @@ int integrate_impl(const chym_problem *prob, const chym_run *run, hipStream_t st
                           cus)) {
         hipError_t e = chym::launch_stage_jfrag(a, v.js, run->steps >= kNarrowSteps, ws, stream);
         if (e == hipSuccess)
-            e = chym::launch_integrate_spack(v.tiles, prob->d, v.xs, v.js, (run->r + pack - 1) / pack, a, ws, nullptr,
-                                             nullptr, nullptr, stream);
+            e = chym::launch_integrate_spack(v.tiles, prob->d, v.xs, v.js, (run->r + pack - 1) / pack, a, ws, stream);
         if (e != hipSuccess) return hip_fail(e, "packed streamed-J integrate launch");
         return CHYM_OK;
     }
@@ -403,7 +402,8 @@ struct Group {
     int d;
     int kind, waves;  // launch plan of this variant (resident kernels)
     int team;         // layout of the team integrator, or chym::kTeamNone
-    bool spack;       // the packed streamed-J kernel
+    bool spack;       // the packed streamed-J kernel (v.tiles: its shape)
+    int branch;       // of the recorded graph
     int item_off, n_items;
     int blocks;
     size_t lds;  // slab kernels: LDS operand area; gather kernel: the largest block's LDS
@@ -457,10 +457,45 @@ int validate_out(const chym_problem *prob, const chym_run *run, const chym_out *
     return CHYM_OK;
 }
 
+// Groups of a recorded batch run side by side on the hardware queues of the
+// process, four by default; a graph with one branch per group is dealt to them
+// in turn, whatever the groups take.  So the graph has kBranches branches, and
+// the groups go to the one that is free first, longest first, by a rough time:
+// a step of the longest item (measured 0.3 us at small N, 7 us at N = 800
+// dense, 1.2 us sparse) times its steps and the rounds of blocks the group's
+// items make.  150 mixed solves of 32 runs: 5.0 ms with a branch per group and
+// a packed streamed-J group per size and D, 3.1 ms now (2.9 ms of it the one
+// such group of N = 800).
+constexpr int kBranches = 4;
+
+void assign_branches(const chym_task *tasks, int cus, BatchLayout *L) {
+    std::vector<std::pair<double, int>> by_time;
+    for (size_t gi = 0; gi < L->groups.size(); ++gi) {
+        const Group &g = L->groups[gi];
+        const chym_task &tk = tasks[L->items[g.item_off].x];
+        const double n = tk.prob.n;
+        const double step = 0.3 + (g.v.ell ? 1e-3 * n : 1e-5 * n * n);
+        by_time.push_back({-step * tk.run.steps * ((g.n_items + cus - 1) / cus), (int)gi});
+    }
+    std::sort(by_time.begin(), by_time.end());
+    double busy[kBranches] = {};
+    std::vector<Group> sorted;
+    for (const auto &t : by_time) {
+        int br = 0;
+        for (int i = 1; i < kBranches; ++i)
+            if (busy[i] < busy[br]) br = i;
+        busy[br] -= t.first;
+        sorted.push_back(L->groups[t.second]);
+        sorted.back().branch = br;
+    }
+    L->groups.swap(sorted);
+}
+
 int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
     if (n_tasks < 1) return fail(CHYM_EINVAL, "n_tasks = %d must be >= 1", n_tasks);
     if (!tasks) return fail(CHYM_EINVAL, "tasks is NULL");
-    // group key (kind, tiles, d, xs, js): kind 0 resident, 1 streamed-J, 2 sparse rows (one group per d)
+    // group key (kind, tiles, d, xs, js): kind 0 resident, 1 streamed-J, 2 sparse rows (one group per d);
+    // 3 streamed-J on the packed kernel (one group per shape, all d)
     typedef std::tuple<int, int, int, int, int> GroupKey;
     auto group_of = [&](int t) {
         const Variant v = variant_of(&tasks[t].prob, &tasks[t].run);
@@ -507,7 +542,7 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         const chym_task &tk = tasks[t];
         const Variant v = variant_of(&tk.prob, &tk.run);
         const GroupKey gk = group_of(t);
-        auto &lst = by_variant[gk];
+        auto &lst = by_variant[!v.ell && load[gk].spack ? GroupKey(3, chym::spack_shape(v.tiles), 0, v.xs, v.js) : gk];
         if (tk.run.steps == 0) continue;
         int slab = 16;
         if (v.ell) {
@@ -529,25 +564,30 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         auto &lst = kv.second;
         if (lst.empty()) continue;
         // longest first: per-item cost is proportional to the task's step count
-        std::stable_sort(lst.begin(), lst.end(), [&](const int2 &a, const int2 &b) {
-            return tasks[a.x].run.steps > tasks[b.x].run.steps;
-        });
+        // (and, in a group of several sizes, to the products of a step)
+        const bool sizes = std::get<0>(kv.first) == 3;
+        auto cost = [&](const int2 &it) {
+            const chym_task &tk = tasks[it.x];
+            return (int64_t)tk.run.steps * (sizes ? (int64_t)tk.prob.n * tk.prob.n : 1);
+        };
+        std::stable_sort(lst.begin(), lst.end(), [&](const int2 &a, const int2 &b) { return cost(a) > cost(b); });
         Group g;
         g.v.ell = std::get<0>(kv.first) == 2;
-        g.v.slab = std::get<0>(kv.first) == 1;
+        g.v.slab = std::get<0>(kv.first) == 1 || std::get<0>(kv.first) == 3;
         g.v.tiles = std::get<1>(kv.first);
         g.d = std::get<2>(kv.first);
         g.v.xs = std::get<3>(kv.first);
         g.v.js = std::get<4>(kv.first);
         g.lds = 0;
-        g.team = g.v.ell ? chym::kTeamNone : load[kv.first].team;
-        g.spack = !g.v.ell && load[kv.first].spack;
+        g.spack = std::get<0>(kv.first) == 3;
+        g.team = g.v.ell || g.spack ? chym::kTeamNone : load[kv.first].team;
         if (g.team != chym::kTeamNone) {
             g.kind = -3;
             g.waves = 0;
         } else if (g.spack) {
             g.kind = -4;
             g.waves = 0;
+            for (const int2 &it : lst) g.lds = std::max(g.lds, chym::spack_lds((tasks[it.x].prob.n + 15) / 16, g.v.xs));
         } else if (g.v.ell) {
             g.kind = -2;
             g.waves = 16;
@@ -567,6 +607,7 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         L->items.insert(L->items.end(), lst.begin(), lst.end());
         L->groups.push_back(g);
     }
+    assign_branches(tasks, cus, L);
     L->total_replicas = 0;
     L->ising_lds = L->hs_lds = 0;
     L->any_readout = L->any_ising = L->any_hs = false;
@@ -634,7 +675,7 @@ struct chym_batch {
 namespace {
 
 // Issues the batch on `main`: zero the work counters, one persistent kernel
-// per variant group (on `branches[i]` when given, forked from and joined
+// per variant group (on its branch when given, forked from and joined
 // back into `main`), then the per-task scoring kernels.
 int issue_batch(const chym_batch *b, hipStream_t main, const std::vector<hipStream_t> *branches,
                 const std::vector<hipEvent_t> *events) {
@@ -654,25 +695,22 @@ int issue_batch(const chym_batch *b, hipStream_t main, const std::vector<hipStre
     list_d += L.n_stage1p;
     if (e == hipSuccess) e = chym::launch_stage_batched(3, false, tasks_d, list_d, L.n_stage3, ncp_d, jfp_d, main);
     if (e != hipSuccess) return hip_fail(e, "stage J");
-    const bool fork = branches && L.groups.size() > 1;
-    if (fork) {
+    const int forks = branches ? (int)std::min<size_t>(L.groups.size(), kBranches) : 1;
+    if (forks > 1) {
         e = hipEventRecord((*events)[0], main);
-        if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
+        for (int i = 0; e == hipSuccess && i < forks; ++i) e = hipStreamWaitEvent((*branches)[i], (*events)[0], 0);
+        if (e != hipSuccess) return hip_fail(e, "fork branches");
     }
     for (size_t gi = 0; gi < L.groups.size(); ++gi) {
         const Group &g = L.groups[gi];
-        hipStream_t s = fork ? (*branches)[gi] : main;
-        if (fork) {
-            e = hipStreamWaitEvent(s, (*events)[0], 0);
-            if (e != hipSuccess) return hip_fail(e, "hipStreamWaitEvent");
-        }
+        hipStream_t s = forks > 1 ? (*branches)[g.branch] : main;
         if (g.team != chym::kTeamNone)
             e = chym::launch_integrate_team(g.team, g.v.tiles, g.d, g.v.xs, g.v.js, false, g.n_items, chym::IntegArgs{},
                                             tasks_d, items_d + g.item_off, s);
         else if (g.spack)
-            e = chym::launch_integrate_spack(g.v.tiles, g.d, g.v.xs, g.v.js, g.n_items, chym::IntegArgs{}, nullptr,
-                                             tasks_d, items_d + g.item_off,
-                                             reinterpret_cast<const void *const *>(b->ws + L.off_jfp), s);
+            e = chym::launch_integrate_spack_batch(g.v.tiles, g.v.xs, g.v.js, g.lds, g.n_items, tasks_d,
+                                                   items_d + g.item_off,
+                                                   reinterpret_cast<const void *const *>(b->ws + L.off_jfp), s);
         else if (g.v.ell)
             e = chym::launch_integrate_ell_persistent(g.d, g.blocks, g.lds, tasks_d, items_d + g.item_off, g.n_items,
                                                       counters + gi, s);
@@ -685,11 +723,11 @@ int issue_batch(const chym_batch *b, hipStream_t main, const std::vector<hipStre
             e = chym::launch_integrate_persistent(g.v.tiles, g.d, g.v.xs, g.v.js, g.kind, g.waves, g.blocks, tasks_d,
                                                   items_d + g.item_off, g.n_items, counters + gi, s);
         if (e != hipSuccess) return hip_fail(e, "persistent integrate launch");
-        if (fork) {
-            e = hipEventRecord((*events)[gi + 1], s);
-            if (e == hipSuccess) e = hipStreamWaitEvent(main, (*events)[gi + 1], 0);
-            if (e != hipSuccess) return hip_fail(e, "join branch");
-        }
+    }
+    for (int i = 0; forks > 1 && i < forks; ++i) {
+        e = hipEventRecord((*events)[i + 1], (*branches)[i]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(main, (*events)[i + 1], 0);
+        if (e != hipSuccess) return hip_fail(e, "join branch");
     }
     if (L.any_readout || L.any_ising || L.any_hs) {
         e = chym::launch_score_batched(reinterpret_cast<const chym::ScoreArgs *>(b->ws + L.off_score),
@@ -908,9 +946,9 @@ int batch_build(const chym_task *tasks, int32_t n_tasks, void *workspace, size_t
         *plan = b;
         return CHYM_OK;
     }
-    // record the launch sequence as a graph with one branch per variant group
+    // record the launch sequence as a graph with branches of groups
     e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);
-    const size_t ng = b->layout.groups.size();
+    const size_t ng = std::min<size_t>(b->layout.groups.size(), kBranches);
     for (size_t i = 0; e == hipSuccess && ng > 1 && i < ng; ++i) {
         hipStream_t s;
         e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);

@@ -332,11 +332,16 @@ hipError_t launch_integrate_slab_persistent(int tiles, int d, int xs, int js, in
 // Packed streamed-J integrator (16 columns per block), for launches of few
 // replicas: whether it takes `blocks` packed blocks on cus compute units
 // (narrow: the couplings are stored in eight bits; batch: in one batch group),
-// and its launch (one problem staged at `stage`, or items of many problems).
+// and the launches: of one problem staged at `stage`, and of items of many
+// problems of any D with one shape (row tiles per wavefront), lds the largest
+// spack_lds among them.
 bool spack_takes(int tiles, int d, int xs, int js, bool narrow, int64_t blocks, bool batch, int cus);
-hipError_t launch_integrate_spack(int tiles, int d, int xs, int js, int blocks, const IntegArgs &one,
-                                  const void *stage, const IntegArgs *tasks, const int2 *items,
-                                  const void *const *stages, hipStream_t stream);
+int spack_shape(int tiles);
+size_t spack_lds(int tiles, int xs);
+hipError_t launch_integrate_spack(int tiles, int d, int xs, int js, int blocks, const IntegArgs &a, const void *stage,
+                                  hipStream_t stream);
+hipError_t launch_integrate_spack_batch(int shape, int xs, int js, size_t lds, int blocks, const IntegArgs *tasks,
+                                        const int2 *items, const void *const *stages, hipStream_t stream);
 
 // Learned early restart: trajectory features and the MLP.
 hipError_t launch_features(int n, int d, int r, const void *j, int j_dtype, const float *x, uint64_t *prev,

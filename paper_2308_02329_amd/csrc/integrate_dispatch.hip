@@ -306,15 +306,18 @@ hipError_t launch_integrate_team(int layout, int tiles, int d, int xs, int js, b
 }
 
 // ------------------------------------------------- packed streamed-J kernels
-static SpackFn lookup_spack(int tiles, int d, int xs, int js) {
+static SpackFn lookup_spack(int tpw, int d, int xs, int js) {
     switch (d) {
-        case 1: return lookup_spack_1(tiles, xs, js);
-        case 2: return lookup_spack_2(tiles, xs, js);
-        case 3: return lookup_spack_3(tiles, xs, js);
-        case 4: return lookup_spack_4(tiles, xs, js);
+        case 1: return lookup_spack_1(tpw, xs, js);
+        case 2: return lookup_spack_2(tpw, xs, js);
+        case 3: return lookup_spack_3(tpw, xs, js);
+        case 4: return lookup_spack_4(tpw, xs, js);
         default: return nullptr;
     }
 }
+
+int spack_shape(int tiles) { return spack_tiles_per_wave(tiles); }
+size_t spack_lds(int tiles, int xs) { return spack_lds_bytes((tiles + 1) / 2, xs); }
 
 // Where the packed kernel is faster than the slab kernel (one problem, slab
 // time / packed time, at N = 260, 512, 800, 1000; +-1 couplings are "narrow"):
@@ -336,7 +339,7 @@ static SpackFn lookup_spack(int tiles, int d, int xs, int js) {
 // slab kernel passes over J once per component (three state terms, D >= 3,
 // more than 32 tiles).
 bool spack_takes(int tiles, int d, int xs, int js, bool narrow, int64_t blocks, bool batch, int cus) {
-    if (!lookup_spack(tiles, d, xs, js)) return false;
+    if (!lookup_spack(spack_shape(tiles), d, xs, js)) return false;
     if (blocks > cus) {
         if (batch || xs != 3 || d < 3 || tiles <= 32) return false;
         return blocks <= (d == 4 && js == 1 ? 3 : 2) * (int64_t)cus;
@@ -346,16 +349,27 @@ bool spack_takes(int tiles, int d, int xs, int js, bool narrow, int64_t blocks, 
     return xs == 3 ? d > 1 : d == 4 && tiles >= 24 && 2 * blocks <= cus;
 }
 
-hipError_t launch_integrate_spack(int tiles, int d, int xs, int js, int blocks, const IntegArgs &one,
-                                  const void *stage, const IntegArgs *tasks, const int2 *items,
-                                  const void *const *stages, hipStream_t stream) {
-    SpackFn fn = lookup_spack(tiles, d, xs, js);
+hipError_t launch_integrate_spack(int tiles, int d, int xs, int js, int blocks, const IntegArgs &a, const void *stage,
+                                  hipStream_t stream) {
+    SpackFn fn = lookup_spack(spack_shape(tiles), d, xs, js);
     if (!fn) return hipErrorInvalidDeviceFunction;
-    const size_t lds = spack_lds_bytes((tiles + 1) / 2, xs);
+    const size_t lds = spack_lds(tiles, xs);
     hipError_t e = slab_prepare(reinterpret_cast<const void *>(fn), lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fn, dim3(blocks), dim3(64 * kSpackWaves), lds, stream, one,
-                       reinterpret_cast<const unsigned char *>(stage), tasks, items,
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(64 * kSpackWaves), lds, stream, a,
+                       reinterpret_cast<const unsigned char *>(stage));
+    return hipGetLastError();
+}
+
+hipError_t launch_integrate_spack_batch(int shape, int xs, int js, size_t lds, int blocks, const IntegArgs *tasks,
+                                        const int2 *items, const void *const *stages, hipStream_t stream) {
+    SpackBatchFn fn = js == 3 ? lookup_spack_batch_3_3(shape)
+                      : xs == 3 ? lookup_spack_batch_3_1(shape)
+                                : lookup_spack_batch_1_1(shape);
+    if (!fn) return hipErrorInvalidDeviceFunction;
+    hipError_t e = slab_prepare(reinterpret_cast<const void *>(fn), lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(64 * kSpackWaves), lds, stream, tasks, items,
                        reinterpret_cast<const unsigned char *const *>(stages));
     return hipGetLastError();
 }

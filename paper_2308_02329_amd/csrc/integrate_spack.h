@@ -229,20 +229,13 @@ __device__ __forceinline__ void integrate_spack(const IntegArgs &a, int rep0, co
         }
 }
 
-// One problem (items = NULL, its staged J at stage0), or block b integrates
-// item b, (task, replica block), of many problems of one shape.
+// Integrates one replica block in the format of its staging (uniform; narrow
+// formats exist for single-term couplings).
 template <int D, int XS, int JS, int TPW>
-__global__ __launch_bounds__(64 * kSpackWaves) __attribute__((amdgpu_waves_per_eu(2)))
-void k_integrate_spack(IntegArgs one, const unsigned char *__restrict__ stage0, const IntegArgs *__restrict__ tasks,
-                       const int2 *__restrict__ items, const unsigned char *const *__restrict__ stages) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    bf16x8 *lb = reinterpret_cast<bf16x8 *>(smem);
-    int2 wi = int2{0, (int)blockIdx.x};
-    if (items) wi = items[blockIdx.x];
-    const IntegArgs a = in_wave(items ? tasks[wi.x] : one);
-    const unsigned char *stage = in_wave(items ? stages[wi.x] : stage0);
+__device__ __forceinline__ void spack_run(const IntegArgs &a, int block, const unsigned char *__restrict__ stage,
+                                          bf16x8 *lb) {
     const int ncp = ((a.n + 15) / 16 + 1) / 2;
-    const int rep0 = wi.y * team_replicas(D, true);
+    const int rep0 = block * team_replicas(D, true);
     if constexpr (JS == 1) {
         const int fmt = __builtin_amdgcn_readfirstlane(stage_format(stage));
         if (fmt == kStageE2M1) {
@@ -257,31 +250,80 @@ void k_integrate_spack(IntegArgs one, const unsigned char *__restrict__ stage0, 
     integrate_spack<D, XS, JS, TPW, kStageBf16>(a, rep0, stage, ncp, lb);
 }
 
-typedef void (*SpackFn)(IntegArgs, const unsigned char *, const IntegArgs *, const int2 *, const unsigned char *const *);
+template <int D, int XS, int JS, int TPW>
+__global__ __launch_bounds__(64 * kSpackWaves) __attribute__((amdgpu_waves_per_eu(2)))
+void k_integrate_spack(IntegArgs a, const unsigned char *__restrict__ stage) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    spack_run<D, XS, JS, TPW>(a, blockIdx.x, stage, reinterpret_cast<bf16x8 *>(smem));
+}
+
+// Many problems: block b integrates item b, (task, replica block).  One launch
+// takes all D: a launch runs few blocks, for long, and only a few launches run
+// side by side.
+template <int XS, int JS, int TPW>
+__global__ __launch_bounds__(64 * kSpackWaves) __attribute__((amdgpu_waves_per_eu(2)))
+void k_integrate_spack_batch(const IntegArgs *__restrict__ tasks, const int2 *__restrict__ items,
+                             const unsigned char *const *__restrict__ stages) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int2 wi = items[blockIdx.x];
+    const IntegArgs a = in_wave(tasks[wi.x]);
+    const unsigned char *stage = in_wave(stages[wi.x]);
+    bf16x8 *lb = reinterpret_cast<bf16x8 *>(smem);
+    switch (a.d) {
+        case 1: return spack_run<1, XS, JS, TPW>(a, wi.y, stage, lb);
+        case 2: return spack_run<2, XS, JS, TPW>(a, wi.y, stage, lb);
+        case 3: return spack_run<3, XS, JS, TPW>(a, wi.y, stage, lb);
+        case 4: return spack_run<4, XS, JS, TPW>(a, wi.y, stage, lb);
+    }
+}
+
+typedef void (*SpackFn)(IntegArgs, const unsigned char *);
+typedef void (*SpackBatchFn)(const IntegArgs *, const int2 *, const unsigned char *const *);
 
 // Beyond the team integrator's sizes: 17 .. 64 row tiles, four, six or eight
 // per wavefront.
 constexpr int kSpackMinTiles = kTeamMaxTiles + 1;
 
-template <int D, int XS, int JS>
-SpackFn spack_lookup_tiles(int tiles) {
-    if (tiles < kSpackMinTiles || tiles > 64) return nullptr;
+inline int spack_tiles_per_wave(int tiles) {
+    if (tiles < kSpackMinTiles || tiles > 64) return 0;
     const int per = (tiles + kSpackWaves - 1) / kSpackWaves;
-    if (per <= 4) return k_integrate_spack<D, XS, JS, 4>;
-    if (per <= 6) return k_integrate_spack<D, XS, JS, 6>;
-    return k_integrate_spack<D, XS, JS, 8>;
+    return per <= 4 ? 4 : per <= 6 ? 6 : 8;
+}
+
+template <int D, int XS, int JS>
+SpackFn spack_lookup_tiles(int tpw) {
+    switch (tpw) {
+        case 4: return k_integrate_spack<D, XS, JS, 4>;
+        case 6: return k_integrate_spack<D, XS, JS, 6>;
+        case 8: return k_integrate_spack<D, XS, JS, 8>;
+        default: return nullptr;
+    }
 }
 
 template <int D>
-SpackFn spack_lookup(int tiles, int xs, int js) {
-    if (js == 3) return spack_lookup_tiles<D, 3, 3>(tiles);
-    return xs == 3 ? spack_lookup_tiles<D, 3, 1>(tiles) : spack_lookup_tiles<D, 1, 1>(tiles);
+SpackFn spack_lookup(int tpw, int xs, int js) {
+    if (js == 3) return spack_lookup_tiles<D, 3, 3>(tpw);
+    return xs == 3 ? spack_lookup_tiles<D, 3, 1>(tpw) : spack_lookup_tiles<D, 1, 1>(tpw);
 }
 
-// One translation unit per D instantiates its kernels.
-SpackFn lookup_spack_1(int tiles, int xs, int js);
-SpackFn lookup_spack_2(int tiles, int xs, int js);
-SpackFn lookup_spack_3(int tiles, int xs, int js);
-SpackFn lookup_spack_4(int tiles, int xs, int js);
+template <int XS, int JS>
+SpackBatchFn spack_batch_lookup(int tpw) {
+    switch (tpw) {
+        case 4: return k_integrate_spack_batch<XS, JS, 4>;
+        case 6: return k_integrate_spack_batch<XS, JS, 6>;
+        case 8: return k_integrate_spack_batch<XS, JS, 8>;
+        default: return nullptr;
+    }
+}
+
+// One translation unit per D instantiates its kernels, one per number of terms
+// those of batches.
+SpackFn lookup_spack_1(int tpw, int xs, int js);
+SpackFn lookup_spack_2(int tpw, int xs, int js);
+SpackFn lookup_spack_3(int tpw, int xs, int js);
+SpackFn lookup_spack_4(int tpw, int xs, int js);
+SpackBatchFn lookup_spack_batch_1_1(int tpw);
+SpackBatchFn lookup_spack_batch_3_1(int tpw);
+SpackBatchFn lookup_spack_batch_3_3(int tpw);
 
 }  // namespace chym

@@ -2,5 +2,5 @@
 #include "integrate_spack.h"
 
 namespace chym {
-SpackFn lookup_spack_1(int tiles, int xs, int js) { return spack_lookup<1>(tiles, xs, js); }
+SpackFn lookup_spack_1(int tpw, int xs, int js) { return spack_lookup<1>(tpw, xs, js); }
 }  // namespace chym

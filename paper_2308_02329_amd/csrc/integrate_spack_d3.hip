@@ -2,5 +2,5 @@
 #include "integrate_spack.h"
 
 namespace chym {
-SpackFn lookup_spack_3(int tiles, int xs, int js) { return spack_lookup<3>(tiles, xs, js); }
+SpackFn lookup_spack_3(int tpw, int xs, int js) { return spack_lookup<3>(tpw, xs, js); }
 }  // namespace chym

@@ -80,3 +80,20 @@ def test_batch_equals_slab(n, d, prec, forms):
 
     for a, b in zip(run(), _chosen(n, d, prec, probs[0]["J"], run)):
         assert _same(a, b)
+
+
+def test_batch_of_all_d_and_sizes_equals_singles():
+    """The packed groups of a batch hold problems of every D and of several
+    sizes, the recorded graph runs them beside the other groups."""
+    shapes = [(257, 1, 5), (390, 2, 11), (512, 3, 7), (300, 4, 3), (800, 4, 6), (770, 2, 9), (40, 3, 20), (130, 2, 8)]
+    probs = [_problem(n, d, r, "i8") for n, d, r in shapes]
+    tasks = [dict(p, x=p["x"].clone(), steps=STEPS - i, precision="f32") for i, p in enumerate(probs)]
+    b = api.chym_batch_create(tasks)
+    for _ in range(2):
+        for t, p in zip(tasks, probs):
+            t["x"].copy_(p["x"])
+        b.launch()
+    torch.cuda.synchronize()
+    b.destroy()
+    for i, (t, p) in enumerate(zip(tasks, probs)):
+        assert _same(t["x"], _single(p, "f32", STEPS - i)), shapes[i]
