@@ -144,7 +144,7 @@ chym::IntegArgs make_args(const chym_problem *prob, const chym_run *run) {
 
 int check_variant(const chym_problem *prob, const chym_run *run) {
     if (prob->j_dtype == CHYM_J_ELL) {
-        if (prob->n > kEllMaxN || chym::ell_replicas_per_block(prob->n, prob->d) == 0)
+        if (prob->n > kEllMaxN || !chym::ell_takes(prob->n, prob->d))
             return fail(CHYM_EUNSUPPORTED, "sparse couplings: n = %d must be <= %d", prob->n, kEllMaxN);
         return CHYM_OK;
     }
@@ -185,7 +185,7 @@ int integrate_impl(const chym_problem *prob, const chym_run *run, hipStream_t st
     if (rc) return rc;
     const chym::IntegArgs a = make_args(prob, run);
     if (prob->j_dtype == CHYM_J_ELL) {
-        hipError_t e = chym::launch_integrate_ell(a, stream);
+        hipError_t e = chym::launch_integrate_ell(a, cus, stream);
         if (e != hipSuccess) return hip_fail(e, "sparse integrate launch");
         return CHYM_OK;
     }
@@ -508,6 +508,7 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         bool narrow = true;  // all couplings in eight bits
     };
     std::map<GroupKey, Load> load;
+    int64_t ell_replicas = 0;  // of all sparse tasks
     std::map<GroupKey, std::vector<int2>> by_variant;
     for (int t = 0; t < n_tasks; ++t) {
         const chym_task &tk = tasks[t];
@@ -519,7 +520,11 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
             std::string m = g_err;
             return fail(rc, "task %d: %s", t, m.c_str());
         }
-        if (tk.run.steps == 0 || variant_of(&tk.prob, &tk.run).ell) continue;
+        if (tk.run.steps == 0) continue;
+        if (variant_of(&tk.prob, &tk.run).ell) {
+            ell_replicas += tk.run.r;
+            continue;
+        }
         Load &ld = load[group_of(t)];
         const int pack = chym::team_block_replicas(chym::kTeamPack, tk.prob.d);
         ld.blocks += (tk.run.r + pack - 1) / pack;
@@ -546,8 +551,12 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         if (tk.run.steps == 0) continue;
         int slab = 16;
         if (v.ell) {
-            slab = chym::ell_replicas_per_block(tk.prob.n, tk.prob.d);
-        } else if (load[gk].team != chym::kTeamNone) {
+            const int lrb = chym::ell_lrb(tk.prob.n, tk.prob.d, ell_replicas, cus);
+            const int blocks = (int)(((int64_t)tk.run.r + (1 << lrb) - 1) >> lrb);
+            for (int g = 0; g < blocks; ++g) lst.push_back(make_int2(t, 8 * g + lrb));
+            continue;
+        }
+        if (load[gk].team != chym::kTeamNone) {
             slab = chym::team_block_replicas(load[gk].team, tk.prob.d);
         } else if (load[gk].spack) {
             slab = chym::team_block_replicas(chym::kTeamPack, tk.prob.d);
@@ -591,7 +600,7 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         } else if (g.v.ell) {
             g.kind = -2;
             g.waves = 16;
-            for (const int2 &it : lst) g.lds = std::max(g.lds, chym::ell_lds_bytes(tasks[it.x].prob.n, g.d));
+            for (const int2 &it : lst) g.lds = std::max(g.lds, chym::ell_lds_bytes(tasks[it.x].prob.n, g.d, it.y & 7));
         } else if (g.v.slab) {
             g.kind = -1;
             g.waves = plan_for(key_of(g.v, g.d)).waves;  // the slab kernel's block size

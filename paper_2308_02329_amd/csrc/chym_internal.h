@@ -237,15 +237,16 @@ hipError_t persistent_occupancy(int tiles, int d, int xs, int js, int kind, int 
 hipError_t launch_zero_counters(int *counters, int n, hipStream_t stream);
 // FP8 (E4M3 + per-row power-of-two) packing of a float32 coupling matrix.
 hipError_t launch_quantize_fp8(int n, const float *j, uint8_t *out, hipStream_t stream);
-// Sparse (ELL) couplings: replicas per block for n, d (0 if n is too large),
-// and the gather integrator.
-int ell_replicas_per_block(int n, int d);
-hipError_t launch_integrate_ell(const IntegArgs &a, hipStream_t stream);
-// LDS bytes of one block of the gather integrator for n, d; the persistent
-// form over many problems of one d (items: task, replica block of
-// ell_replicas_per_block(n, d) replicas), launched with the largest LDS
-// size of its tasks.
-size_t ell_lds_bytes(int n, int d);
+// Sparse (ELL) couplings: whether the gather integrator takes n and d, its
+// replicas per block (log2) where r replicas run on cus compute units, and its
+// launch.
+bool ell_takes(int n, int d);
+int ell_lrb(int n, int d, int64_t r, int cus);
+hipError_t launch_integrate_ell(const IntegArgs &a, int cus, hipStream_t stream);
+// LDS bytes of one block; the persistent form over many problems of one d
+// (items: task, 8 x replica block + log2 of its replicas), launched with the
+// largest LDS size of its items.
+size_t ell_lds_bytes(int n, int d, int lrb);
 hipError_t ell_persistent_occupancy(int d, size_t lds, int *blocks_per_cu);
 hipError_t launch_integrate_ell_persistent(int d, int blocks, size_t lds, const IntegArgs *tasks, const int2 *items,
                                            int n_items, int *counter, hipStream_t stream);
