@@ -461,21 +461,34 @@ int validate_out(const chym_problem *prob, const chym_run *run, const chym_out *
 // process, four by default; a graph with one branch per group is dealt to them
 // in turn, whatever the groups take.  So the graph has kBranches branches, and
 // the groups go to the one that is free first, longest first, by a rough time:
-// a step of the longest item (measured 0.3 us at small N, 7 us at N = 800
-// dense, 1.2 us sparse) times its steps and the rounds of blocks the group's
-// items make.  150 mixed solves of 32 runs: 5.0 ms with a branch per group and
-// a packed streamed-J group per size and D, 3.1 ms now (2.9 ms of it the one
-// such group of N = 800).
+// that of all its items, one at a time on every compute unit, or of its longest
+// item.  A step of an item, in us, from what was measured at N = 100 to 800:
+// 0.3 + 1e-3 n (sparse), + 2.2e-5 n^2 (slab), + 1e-5 n^2 (the other dense ones),
+// twice and four times that for three state terms with one and three coupling
+// terms.  150 mixed solves of 32 runs: 5.0 ms with a branch per group and a
+// packed streamed-J group per size and D, 3.1 ms now (2.9 ms of it the one such
+// group of N = 800); 10 000 such solves of 5000 steps, tuned: 1.02 s, 1.16 s
+// one group after another.
 constexpr int kBranches = 4;
+
+double item_time(const Group &g, const chym_task &tk) {
+    const double n = tk.prob.n;
+    if (g.v.ell) return tk.run.steps * (0.3 + 1e-3 * n);
+    const double terms = g.v.js == 3 ? 4.0 : g.v.xs == 3 ? 2.0 : 1.0;
+    return tk.run.steps * (0.3 + terms * (g.v.slab && !g.spack ? 2.2e-5 : 1e-5) * n * n);
+}
 
 void assign_branches(const chym_task *tasks, int cus, BatchLayout *L) {
     std::vector<std::pair<double, int>> by_time;
     for (size_t gi = 0; gi < L->groups.size(); ++gi) {
         const Group &g = L->groups[gi];
-        const chym_task &tk = tasks[L->items[g.item_off].x];
-        const double n = tk.prob.n;
-        const double step = 0.3 + (g.v.ell ? 1e-3 * n : 1e-5 * n * n);
-        by_time.push_back({-step * tk.run.steps * ((g.n_items + cus - 1) / cus), (int)gi});
+        double longest = 0.0, all = 0.0;
+        for (int i = 0; i < g.n_items; ++i) {
+            const double t = item_time(g, tasks[L->items[g.item_off + i].x]);
+            longest = std::max(longest, t);
+            all += t / cus;
+        }
+        by_time.push_back({-std::max(longest, all), (int)gi});
     }
     std::sort(by_time.begin(), by_time.end());
     double busy[kBranches] = {};
@@ -857,7 +870,8 @@ int map_batch_layout(const chym_map_problem *probs, const chym_run *runs, int32_
     }
     L->off_tasks = 0;
     L->off_items = align_up(sizeof(chym::IntegArgs) * (size_t)n_tasks);
-    L->total = L->off_items + align_up(sizeof(int2) * std::max<size_t>(1, L->items.size()));
+    // and an unused third area: a workspace was never less than three
+    L->total = L->off_items + align_up(sizeof(int2) * std::max<size_t>(1, L->items.size())) + kAlign;
     return CHYM_OK;
 }
 

@@ -67,10 +67,12 @@ static int ell_max_lrb(int n, int d) {
 
 bool ell_takes(int n, int d) { return ell_max_lrb(n, d) >= 0; }
 
-// The time of a launch goes with the rounds of blocks and the units of a block.
+// The time of a launch goes with the rounds of blocks, and that of a block's
+// step with its units and what a step takes without any: 0.2 us, as long as
+// 700 units.
 int ell_lrb(int n, int d, int64_t r, int cus) {
     int best = ell_max_lrb(n, d);
-    auto time = [&](int l) { return ((((r + (1 << l) - 1) >> l) + cus - 1) / cus) << l; };
+    auto time = [&](int l) { return ((((r + (1 << l) - 1) >> l) + cus - 1) / cus) * (700 + ((int64_t)n << l)); };
     for (int l = best - 1; l >= 0; --l)
         if (time(l) < time(best)) best = l;
     return best;
