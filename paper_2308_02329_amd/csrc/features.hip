@@ -39,7 +39,7 @@ __device__ __forceinline__ T wsum(T v) {
 // Features of RB replicas (consecutive, lanes) by a block of RB * 16 threads.
 // The per-replica wavefront that this replaces read the state with a stride of
 // a whole row between lanes and J once per replica (N = 200, D = 3, 20000
-// replicas: 632 us a checkpoint; now 71 us).
+// replicas: 632 us a checkpoint; now 67 us).
 //
 // Every sum keeps its order: it runs over the 64 classes q mod 64, each class
 // in ascending q, then over the classes by halving (32, 16, .. 1).
@@ -51,9 +51,11 @@ __device__ __forceinline__ T wsum(T v) {
 //      16 replicas at a time on v_mfma_f32_16x16x4_f32, whose result is the
 //      chain of four fused multiply-adds in ascending p (checked bit for bit
 //      on the chip, denormals included), so that G and h round as a loop of
-//      fmaf over p.  Wavefront w takes the column tiles I = w mod 4 and the
-//      replica group w / 4: its classes 16 (I mod 4) + 4 g + v are the rows of
-//      its results.
+//      fmaf over p.  With int8 couplings h is a sum of integers below 2^24,
+//      the same in any arithmetic, and comes from the int8 products, at a
+//      sixteenth of the time.  Wavefront w takes the column tiles of one residue
+//      mod 4 and the replica group w / 4: its classes 16 (I mod 4) + 4 g + v are
+//      the rows of its results.
 constexpr int kFeatThreads = 16;  // threads per replica
 constexpr int kFeatUnroll = 8;    // products in flight
 
@@ -87,10 +89,14 @@ __device__ __forceinline__ void feat_products(int n, const void *__restrict__ j,
     const int col = lane & 15, g = lane >> 4;
     const int nt = (n + 15) >> 4;
     const int rep = 16 * (w >> 2) + col;
+    // the classes of most tiles go to other SIMDs for the other replicas and blocks
+    const int cls = (w + 2 * (w >> 2) + blockIdx.x) & 3;
+    constexpr bool INT = JT == CHYM_J_I8;
     float quad[4] = {0.0f, 0.0f, 0.0f, 0.0f}, eis[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int I = w & 3; I < nt; I += 4) {
+    for (int I = cls; I < nt; I += 4) {
         const int q = 16 * I + col;
         f32x4 G = {0.0f, 0.0f, 0.0f, 0.0f}, H = {0.0f, 0.0f, 0.0f, 0.0f};
+        i32x4 HI = {0, 0, 0, 0};
         for (int p0 = 0; p0 < n; p0 += 4 * kFeatUnroll) {
             float a[kFeatUnroll], b[kFeatUnroll];
 #pragma unroll
@@ -103,9 +109,22 @@ __device__ __forceinline__ void feat_products(int n, const void *__restrict__ j,
 #pragma unroll
             for (int m = 0; m < kFeatUnroll; ++m) {
                 G = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m], b[m], G, 0, 0, 0);
-                H = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m], b[m] >= 0.0f ? 1.0f : -1.0f, H, 0, 0, 0);
+                if constexpr (!INT)
+                    H = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m], b[m] >= 0.0f ? 1.0f : -1.0f, H, 0, 0, 0);
+            }
+            if constexpr (INT) {
+                // the row p0 + 4 m + g in byte m of lane group g, on both sides
+                uint32_t pa[2] = {0u, 0u}, pb[2] = {0u, 0u};
+#pragma unroll
+                for (int m = 0; m < kFeatUnroll; ++m) {
+                    pa[m >> 2] |= ((uint32_t)(int)a[m] & 0xffu) << (8 * (m & 3));
+                    pb[m >> 2] |= (b[m] >= 0.0f ? 0x01u : 0xffu) << (8 * (m & 3));
+                }
+                HI = __builtin_amdgcn_mfma_i32_16x16x32_i8((long)((uint64_t)pa[1] << 32 | pa[0]),
+                                                           (long)((uint64_t)pb[1] << 32 | pb[0]), HI, 0, 0, 0);
             }
         }
+        if constexpr (INT) H = f32x4{(float)HI[0], (float)HI[1], (float)HI[2], (float)HI[3]};
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int qr = 16 * I + 4 * g + v;
@@ -118,8 +137,8 @@ __device__ __forceinline__ void feat_products(int n, const void *__restrict__ j,
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        ca[(16 * (w & 3) + 4 * g + v) * RB + rep] = quad[v];
-        cb[(16 * (w & 3) + 4 * g + v) * RB + rep] = eis[v];
+        ca[(16 * cls + 4 * g + v) * RB + rep] = quad[v];
+        cb[(16 * cls + 4 * g + v) * RB + rep] = eis[v];
     }
 }
 
