@@ -39,7 +39,7 @@ __device__ __forceinline__ T wsum(T v) {
 // Features of RB replicas (consecutive, lanes) by a block of RB * 16 threads.
 // The per-replica wavefront that this replaces read the state with a stride of
 // a whole row between lanes and J once per replica (N = 200, D = 3, 20000
-// replicas: 632 us a checkpoint; now 67 us).
+// replicas: 632 us a checkpoint; now 58 us).
 //
 // Every sum keeps its order: it runs over the 64 classes q mod 64, each class
 // in ascending q, then over the classes by halving (32, 16, .. 1).
@@ -82,6 +82,38 @@ __device__ __forceinline__ void class_tree(float *ca, float *cb) {
     __syncthreads();
 }
 
+// The couplings a[m] = J[p0 + 4 m + g][q0 + col] of an int8 matrix, zero outside
+// it: the four lanes of a quad read four bytes of four rows each, a row in
+// one read, and take their column's byte from each other's (a byte read per
+// lane and row takes the address unit four times as long: 67 us a checkpoint
+// of the above against 58).
+__device__ __forceinline__ void feat_rows_i8(int n, const int8_t *__restrict__ j, int p0, int g, int q0, int col,
+                                             float (&a)[kFeatUnroll]) {
+    const int lane4 = col & 3;
+    const int qa = q0 + col - lane4;  // the quad's first column
+#pragma unroll
+    for (int t = 0; t < kFeatUnroll; t += 4) {
+        const int p = p0 + 4 * (t + lane4) + g;
+        uint32_t own = 0u;
+        if (p < n) {
+            const int8_t *row = j + (size_t)p * n + qa;
+            if (qa + 4 <= n) {
+                __builtin_memcpy(&own, row, 4);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    if (qa + c < n) own |= (uint32_t)(uint8_t)row[c] << (8 * c);
+            }
+        }
+        const uint32_t s[4] = {(uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0x00, 0xf, 0xf, true),
+                               (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0x55, 0xf, 0xf, true),
+                               (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xaa, 0xf, 0xf, true),
+                               (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xff, 0xf, 0xf, true)};
+#pragma unroll
+        for (int m = 0; m < 4; ++m) a[t + m] = (float)((int32_t)(s[m] << (24 - 8 * lane4)) >> 24);
+    }
+}
+
 template <int RB, int JT>
 __device__ __forceinline__ void feat_products(int n, const void *__restrict__ j, const float *sx, float *ca, float *cb) {
     const int lane = threadIdx.x & 63;
@@ -99,11 +131,14 @@ __device__ __forceinline__ void feat_products(int n, const void *__restrict__ j,
         i32x4 HI = {0, 0, 0, 0};
         for (int p0 = 0; p0 < n; p0 += 4 * kFeatUnroll) {
             float a[kFeatUnroll], b[kFeatUnroll];
+            if constexpr (INT) feat_rows_i8(n, reinterpret_cast<const int8_t *>(j), p0, g, 16 * I, col, a);
 #pragma unroll
             for (int m = 0; m < kFeatUnroll; ++m) {
                 const int p = p0 + 4 * m + g;
-                const float v = feat_coupling<JT>(j, n, min(p, n - 1), min(q, n - 1));
-                a[m] = p < n && q < n ? v : 0.0f;
+                if constexpr (!INT) {
+                    const float v = feat_coupling<JT>(j, n, min(p, n - 1), min(q, n - 1));
+                    a[m] = p < n && q < n ? v : 0.0f;
+                }
                 b[m] = sx[p * RB + rep];
             }
 #pragma unroll
