@@ -466,7 +466,7 @@ int validate_out(const chym_problem *prob, const chym_run *run, const chym_out *
 // 0.3 + 1e-3 n (sparse), + 2.2e-5 n^2 (slab), + 1e-5 n^2 (the other dense ones),
 // twice and four times that for three state terms with one and three coupling
 // terms.  150 mixed solves of 32 runs: 5.0 ms with a branch per group and a
-// packed streamed-J group per size and D, 3.1 ms now (2.9 ms of it the one such
+// packed streamed-J group per size and D, 2.8 ms now (2.5 ms of it the one such
 // group of N = 800); 10 000 such solves of 5000 steps, tuned: 1.02 s, 1.16 s
 // one group after another.
 constexpr int kBranches = 4;

@@ -323,15 +323,15 @@ size_t spack_lds(int tiles, int xs) { return spack_lds_bytes((tiles + 1) / 2, xs
 // time / packed time, at N = 260, 512, 800, 1000; +-1 couplings are "narrow"):
 //                                packed blocks per CU    0.25 - 1            2
 //   three state terms, D = 4, narrow          1.9 - 2.1, 3.9 - 4.5,    1.0, 2.1,
-//                                             3.6 - 4.5, 3.9 - 5.0     1.9, 2.1
+//                                             4.1 - 5.2, 4.0 - 5.0     2.1, 2.1
 //   the same, D = 2                           1.4 - 1.6, 1.6 - 1.7,    0.8, 0.9,
-//                                             1.6 - 1.8, 2.0 - 2.2     0.9, 1.1
+//                                             1.8 - 2.0, 2.0 - 2.2     1.0, 1.1
 //   three coupling terms, D = 4               1.3 - 1.6, 2.9 - 3.7,    0.7, 1.5,
-//                                             2.4 - 3.2, 3.3 - 4.2     1.3, 1.7
+//                                             2.9 - 3.6, 3.4 - 4.0     1.4, 1.7
 //   the same, D = 1                           1.0 - 1.1, 1.0, 0.9 - 1.0, 0.9 - 1.0
 //   one state term, D = 4, narrow             1.0 - 1.1, 1.8 - 2.0,    0.7, 1.1,
-//                                             1.6 - 1.8, 2.0 - 2.3     0.9, 1.1
-//   the same, bf16 couplings                  0.8, 1.1 - 1.2, 1.0 - 1.1, 1.0 - 1.3
+//                                             1.9 - 2.2, 1.9 - 2.3     1.0, 1.1
+//   the same, bf16 couplings                  0.8, 1.1 - 1.2, 1.0 - 1.3, 1.0 - 1.3
 //   the same, D = 1                           0.95, 1.0, 1.0, 0.95
 // A block streams all of J either way, so with D = 1 or one state term, where
 // the slab's products are no more than that stream costs, only narrow

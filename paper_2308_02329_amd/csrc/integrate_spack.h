@@ -280,21 +280,24 @@ void k_integrate_spack_batch(const IntegArgs *__restrict__ tasks, const int2 *__
 typedef void (*SpackFn)(IntegArgs, const unsigned char *);
 typedef void (*SpackBatchFn)(const IntegArgs *, const int2 *, const unsigned char *const *);
 
-// Beyond the team integrator's sizes: 17 .. 64 row tiles, four, six or eight
-// per wavefront.
+// Beyond the team integrator's sizes: 17 .. 64 row tiles, three to eight per
+// wavefront.  (A wavefront computes all its tiles' places: at N = 800, 50 tiles,
+// seven places take 6.2 us a step where eight take 7.1, one state term, D = 4.)
 constexpr int kSpackMinTiles = kTeamMaxTiles + 1;
 
 inline int spack_tiles_per_wave(int tiles) {
     if (tiles < kSpackMinTiles || tiles > 64) return 0;
-    const int per = (tiles + kSpackWaves - 1) / kSpackWaves;
-    return per <= 4 ? 4 : per <= 6 ? 6 : 8;
+    return (tiles + kSpackWaves - 1) / kSpackWaves;
 }
 
 template <int D, int XS, int JS>
 SpackFn spack_lookup_tiles(int tpw) {
     switch (tpw) {
+        case 3: return k_integrate_spack<D, XS, JS, 3>;
         case 4: return k_integrate_spack<D, XS, JS, 4>;
+        case 5: return k_integrate_spack<D, XS, JS, 5>;
         case 6: return k_integrate_spack<D, XS, JS, 6>;
+        case 7: return k_integrate_spack<D, XS, JS, 7>;
         case 8: return k_integrate_spack<D, XS, JS, 8>;
         default: return nullptr;
     }
@@ -309,8 +312,11 @@ SpackFn spack_lookup(int tpw, int xs, int js) {
 template <int XS, int JS>
 SpackBatchFn spack_batch_lookup(int tpw) {
     switch (tpw) {
+        case 3: return k_integrate_spack_batch<XS, JS, 3>;
         case 4: return k_integrate_spack_batch<XS, JS, 4>;
+        case 5: return k_integrate_spack_batch<XS, JS, 5>;
         case 6: return k_integrate_spack_batch<XS, JS, 6>;
+        case 7: return k_integrate_spack_batch<XS, JS, 7>;
         case 8: return k_integrate_spack_batch<XS, JS, 8>;
         default: return nullptr;
     }

@@ -51,9 +51,9 @@ def _same(a, b):
     return torch.equal(a.view(torch.int32), b.view(torch.int32))
 
 
-# 17 tiles, the wavefronts' tile counts at their edges (32|33, 48|49), the largest operand in two LDS buffers
+# 17 tiles, the wavefronts' tile counts at their edges (24|25, .. 56|57), the largest operand in two LDS buffers
 # (26|27 chunks for three terms), and the largest problem
-@pytest.mark.parametrize("n", [257, 272, 400, 512, 513, 768, 769, 832, 833, 1000, 1024])
+@pytest.mark.parametrize("n", [257, 272, 384, 385, 400, 512, 513, 640, 641, 768, 769, 832, 833, 896, 897, 1000, 1024])
 @pytest.mark.parametrize("prec,form", [("f32", "i8"), ("f32", "fp8"), ("f32", "bf16"), ("f32", "f32"), ("bf16", "i8"),
                                        ("bf16", "bf16")])
 def test_single_equals_slab(n, prec, form):
