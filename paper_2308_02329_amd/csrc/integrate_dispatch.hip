@@ -273,7 +273,11 @@ int team_layout(int tiles, int d, int xs, int js, int64_t blocks, int64_t waves,
     if (!lookup_team(tiles, d, xs, js, true, map)) return kTeamNone;
     const int nc = (tiles + 1) / 2;
     const bool wave = map ? tiles <= kMapMaxTiles : tiles <= resident_tile_limit(d, xs, js);
-    if (nc == 1 && d == 1 && !map) return kTeamNone;  // the same work in the same single wavefront
+    // D = 1, N <= 32: the same work in the same single wavefront. With one state
+    // term blocks of one wavefront are faster than of four (400 steps, 3489
+    // replicas: N = 9 50 against 64 us, N = 32 67 against 70; 16384 replicas: 67
+    // against 62, 65 against 73), with three they are not (66 and 64 us).
+    if (nc == 1 && d == 1 && xs == 3 && !map) return kTeamNone;
     if (wave && !map && (nc > 1 || tuned)) {
         const int64_t full = (int64_t)4 * cus;
         const int64_t steps = tuned ? 1 : (waves + full - 1) / full;
