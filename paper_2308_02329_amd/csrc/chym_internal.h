@@ -199,6 +199,10 @@ __device__ __forceinline__ IntegArgs in_wave(const IntegArgs &t) {
     return a;
 }
 
+// The most blocks of one launch: HIP takes fewer than 2^32 threads in a
+// dimension, and cuts a larger grid short without an error.
+constexpr int max_blocks(int threads) { return (int)((1ll << 31) / threads); }
+
 // Host-side launcher of the resident integrator for one (tiles, d, xs, js)
 // variant; returns hipSuccess or the launch error.
 hipError_t launch_integrate(int tiles, int d, int xs, int js, int waves_per_block,

@@ -492,7 +492,11 @@ hipError_t launch_sign_words(int n, int d, int r, const float *x, uint64_t *word
 
 hipError_t launch_standardize(int groups, int group, const float *in, float *out, hipStream_t stream) {
     if (groups <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_standardize, dim3(groups, kFeat / kStdCols), dim3(256 * kStdCols), 0, stream, group, in, out);
+    for (int g = 0; g < groups; g += max_blocks(256 * kStdCols)) {
+        const size_t at = (size_t)g * group * kFeat;
+        hipLaunchKernelGGL(k_standardize, dim3(std::min(groups - g, max_blocks(256 * kStdCols)), kFeat / kStdCols),
+                           dim3(256 * kStdCols), 0, stream, group, in + at, out + at);
+    }
     return hipGetLastError();
 }
 

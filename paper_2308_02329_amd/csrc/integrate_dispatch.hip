@@ -1,4 +1,6 @@
 // Host-side dispatch of the register-resident integrator variants.
+#include <algorithm>
+
 #include "integrate_slab.h"
 #include "integrate_spack.h"
 
@@ -304,8 +306,10 @@ hipError_t launch_integrate_team(int layout, int tiles, int d, int xs, int js, b
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(fn, dim3(blocks), dim3(64 * team_waves(nc, team_tiles(tiles, xs, pack))), lds, stream, one, tasks,
-                       items);
+    const int threads = 64 * team_waves(nc, team_tiles(tiles, xs, pack));
+    for (int first = 0; first < blocks; first += max_blocks(threads))
+        hipLaunchKernelGGL(fn, dim3(std::min(blocks - first, max_blocks(threads))), dim3(threads), lds, stream, one, first,
+                           tasks, items ? items + first : nullptr);
     return hipGetLastError();
 }
 

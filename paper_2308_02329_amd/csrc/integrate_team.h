@@ -323,14 +323,14 @@ constexpr int team_wpe() {
 }
 
 // One problem (items = NULL): block b integrates its replicas from
-// b * team_replicas on.  Many problems of one shape: block b integrates item b,
+// (first + b) * team_replicas on.  Many problems of one shape: block b integrates item b,
 // (task, replica block); the host lists the longest tasks first, and the
 // hardware hands the blocks out in that order.
 template <int D, int XS, int JS, int NC, int TW, bool PACK, bool MAP, int WPE = team_wpe<D, XS, JS, NC, TW, PACK>()>
 __global__ __launch_bounds__(64 * team_waves(NC, TW)) __attribute__((amdgpu_waves_per_eu(WPE)))
-void k_integrate_team(IntegArgs one, const IntegArgs *__restrict__ tasks, const int2 *__restrict__ items) {
+void k_integrate_team(IntegArgs one, int first, const IntegArgs *__restrict__ tasks, const int2 *__restrict__ items) {
     extern __shared__ __align__(16) unsigned char smem[];
-    int2 w = int2{0, (int)blockIdx.x};
+    int2 w = int2{0, first + (int)blockIdx.x};
     if (items) w = items[blockIdx.x];
     const IntegArgs a = in_wave(items ? tasks[w.x] : one);
     integrate_team<D, XS, JS, NC, TW, PACK, MAP>(a, w.y * team_replicas(D, PACK), reinterpret_cast<bf16x8 *>(smem));
@@ -339,7 +339,7 @@ void k_integrate_team(IntegArgs one, const IntegArgs *__restrict__ tasks, const 
 // Largest row-tile count of the team kernels (N <= 256).
 constexpr int kTeamMaxTiles = 16;
 
-typedef void (*TeamFn)(IntegArgs, const IntegArgs *, const int2 *);
+typedef void (*TeamFn)(IntegArgs, int, const IntegArgs *, const int2 *);
 
 // The plane layout's operand of all D components must fit LDS twice; D = 1
 // has the packed layout only (they coincide).

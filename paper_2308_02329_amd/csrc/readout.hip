@@ -104,11 +104,11 @@ __device__ __forceinline__ void readout_any(int n, int d, int r, int rep, bool m
     }
 }
 
-__global__ __launch_bounds__(1024) void k_readout(int n, int d, int r, const float *__restrict__ x,
+__global__ __launch_bounds__(1024) void k_readout(int n, int d, int r, int first, const float *__restrict__ x,
                                                   uint64_t *__restrict__ spins, double *__restrict__ extra,
                                                   uint8_t *__restrict__ diverged) {
     __shared__ ReadoutLds sm;
-    const int rep = blockIdx.x * 64 + (threadIdx.x & 63);
+    const int rep = first + blockIdx.x * 64 + (threadIdx.x & 63);
     readout_any(n, d, r, rep, rep < r, blockDim.x >> 6, x, spins, extra, diverged, sm);
 }
 
@@ -535,7 +535,10 @@ __global__ __launch_bounds__(kEnergyThreads) void k_hs_batched(const ScoreArgs *
 hipError_t launch_readout(int n, int d, int r, const float *x, uint64_t *spins, double *extra, uint8_t *diverged,
                           hipStream_t stream) {
     const int waves = std::min(16, (n + 15) / 16);  // 16 rows each
-    hipLaunchKernelGGL(k_readout, dim3((r + 63) / 64), dim3(64 * waves), 0, stream, n, d, r, x, spins, extra, diverged);
+    const int blocks = (r + 63) / 64;
+    for (int b = 0; b < blocks; b += max_blocks(64 * waves))
+        hipLaunchKernelGGL(k_readout, dim3(std::min(blocks - b, max_blocks(64 * waves))), dim3(64 * waves), 0, stream, n, d, r,
+                           64 * b, x, spins, extra, diverged);
     return hipGetLastError();
 }
 
@@ -548,8 +551,14 @@ static hipError_t allow_lds(F fn, size_t lds) {
 hipError_t launch_ising_energy(int n, int r, const void *j, int j_dtype, const uint64_t *spins, int32_t *e_i32,
                                double *e_f64, hipStream_t stream) {
     if (j_dtype == CHYM_J_I8) {
-        hipLaunchKernelGGL(k_ising_energy_i8, dim3((r + 15) / 16), dim3(kEnergyThreads), 0, stream, n, r,
-                           reinterpret_cast<const int8_t *>(j), spins, e_i32, e_f64);
+        const int part = 16 * max_blocks(kEnergyThreads);
+        for (int r0 = 0; r0 < r; r0 += part) {
+            const int k = std::min(r - r0, part);
+            hipLaunchKernelGGL(k_ising_energy_i8, dim3((k + 15) / 16), dim3(kEnergyThreads), 0, stream, n, k,
+                               reinterpret_cast<const int8_t *>(j), spins + (size_t)r0 * ((n + 63) / 64),
+                               e_i32 ? e_i32 + r0 : nullptr, e_f64 ? e_f64 + r0 : nullptr);
+            if (k == r - r0) break;  // r0 + part may pass the largest int
+        }
     } else if (quad_takes(n, j_dtype)) {
         const size_t lds = quad_lds_bytes(n);
         hipError_t e = allow_lds(k_quad, lds);

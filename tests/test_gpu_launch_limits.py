@@ -1,0 +1,51 @@
+"""Replica and group counts whose launches pass 2^32 threads in one dimension
+if a block is launched per few of them."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2308_02329_amd import api  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def test_ising_energies_of_many_replicas():
+    n, r = 3, (1 << 28) + 37
+    J = torch.tensor([[0, 1, -2], [1, 0, 3], [-2, 3, 0]], dtype=torch.int8, device=DEV)
+    spins = torch.arange(r, dtype=torch.int64, device=DEV) % 8
+    e = torch.full((r,), 99, dtype=torch.int32, device=DEV)
+    api.chym_ising_energy(J, spins[:, None], e, None)
+    s = np.array([[1 if w >> p & 1 else -1 for p in range(n)] for w in range(8)])
+    want = torch.from_numpy(-np.einsum("wp,pq,wq->w", s, J.cpu().numpy().astype(int), s).astype(np.int32)).to(DEV)
+    for at in range(0, r, 1 << 26):
+        assert torch.equal(e[at:at + (1 << 26)], want[spins[at:at + (1 << 26)]])
+
+
+def test_standardize_of_many_groups():
+    groups, group = (1 << 22) + 5, 2
+    f = torch.rand((groups * group, 32), device=DEV)
+    f[1::2] = f[::2] + 1.0 + f[1::2]
+    out = api.chym_feature_standardize(f, group)
+    # two values a and b > a: mean and deviation to a few roundings of b, over b - a >= 1
+    assert bool((out[::2] + 1.0).abs().max() <= 1e-5) and bool((out[1::2] - 1.0).abs().max() <= 1e-5)
+
+
+def test_map_of_many_replicas():
+    """A packed block of 256 threads takes 8 replicas at N = 33, D = 2."""
+    n, d, r = 33, 2, (1 << 27) + 19
+    g = np.random.default_rng(5)
+    J = np.triu(g.choice([-1, 1], (n, n)), 1)
+    J = torch.from_numpy((J + J.T).astype(np.int8)).to(DEV)
+    x = torch.empty((n, r, d), device=DEV).uniform_(-0.05, 0.05)
+    h = torch.empty(r, device=DEV).uniform_(0.1, 0.4)
+    some = torch.cat([torch.arange(40), torch.arange((1 << 27) - 20, r)]).to(DEV)
+    xs, hs = x[:, some].contiguous(), h[some].contiguous()
+    kw = dict(b=0.01, loss=0.01, kl=0.1, beta_b2=25.0, jmag=1.0, steps=1)
+    alpha = torch.ones((1, d), device=DEV)
+    before = xs.clone()
+    api.chym_map_integrate(J, h, x, alpha, **kw)
+    api.chym_map_integrate(J, hs, xs, alpha, **kw)
+    assert not torch.equal(xs, before)
+    assert torch.equal(x[:, some].view(torch.int32), xs.view(torch.int32))
