@@ -75,21 +75,26 @@ __device__ __forceinline__ float quad_norm(float x2) {
 
 // Gain of the nonlinear medium for a field of amplitude A under pump h:
 // K = P / (P cosh(kl P) - h sinh(kl P)), P = sqrt(h^2 + A^2), written as
-// 2 P e / ((P + h) + (P - h) e^2) with e = exp(kl P); with P - h = A^2 / (P + h)
-// and both terms multiplied by s = P + h this is 2 P e s / (s^2 + A^2 e^2),
-// which has no cancellation for h >= 0 and needs one reciprocal.  The square
-// root, reciprocal and exponential are the hardware's (each within about
-// 1 ulp); kl2 = kl log2(e).  A select rather than a branch at the end lets the
-// rows of a lane run side by side (N = 14, D = 1, 16384 replicas: 0.38 us a
-// step, 0.60 with branches).
-__device__ __forceinline__ float nlm_gain(float A, float h, float kl2) {
+// 2 P e / ((P + h) + (P - h) e^2) with e = exp(kl P).  For h >= 0, with
+// P - h = A^2 / s and both terms multiplied by s = P + h, this is
+// 2 P e s / (s^2 + A^2 e^2), which has no cancellation and needs one reciprocal.
+// For h < 0 the same with s = P + |h| and e = exp(-kl P) (P + h = A^2 / s, then
+// both sides times e^-2).  ha = |h|, kl2 = kl log2(e) with the sign of h, tiny =
+// 2^-60.  The
+// square root, reciprocal and exponential are the hardware's (each within about
+// 1 ulp).  Below s = 2^-60 the squares leave the normal floats (at h = 0 the
+// reciprocal would overflow from |A| = 4e-20 down) and the gain is 1 to within
+// 2^-60 kl.  A select rather than a branch at the end lets the rows of a lane
+// run side by side (N = 14, D = 1, 16384 replicas: 0.38 us a step, 0.60 with
+// branches).
+__device__ __forceinline__ float nlm_gain(float A, float ha, float kl2, float tiny) {
     const float A2 = A * A;
-    const float P = __builtin_amdgcn_sqrtf(fmaf(h, h, A2));
-    const float s = P + h;
+    const float P = __builtin_amdgcn_sqrtf(fmaf(ha, ha, A2));
+    const float s = P + ha;
     const float e = __builtin_amdgcn_exp2f(kl2 * P);
     const float den = fmaf(A2, e * e, s * s);
     const float k = (2.0f * P * e * s) * __builtin_amdgcn_rcpf(den);
-    return s > 0.0f ? k : 1.0f;  // A = h = 0: the medium is transparent
+    return s > tiny ? k : 1.0f;
 }
 
 // Writes the operand terms of one tile and plane (the lane's four rows, v) into
@@ -150,7 +155,9 @@ __device__ __forceinline__ void integrate_team(const IntegArgs &a, int rep0, bf1
 
     const float base = valid ? (MAP ? a.c0 : fmaf(a.dt, a.pump[rep] - 1.0f, 1.0f)) : 0.0f;
     const float hmap = (MAP && valid) ? a.pump[rep] : 0.0f;
-    const float kl2 = a.kl * 1.44269504088896340736f;  // kl log2(e)
+    const float kl2 = (hmap < 0.0f ? -a.kl : a.kl) * 1.44269504088896340736f;  // kl log2(e), with the sign of h
+    float tiny = 0x1p-60f;
+    if constexpr (MAP) asm("" : "+s"(tiny));  // in a register: as a literal it makes each compare 8 bytes long
     const float nbd = -(a.dt * a.btil);
     const float ned = -(a.dt * a.eta);
     const float dte = a.dt * a.eps;
@@ -180,7 +187,7 @@ __device__ __forceinline__ void integrate_team(const IntegArgs &a, int rep0, bf1
 #pragma unroll
                 for (int mu = 0; mu < P; ++mu)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) x[i][mu][v] = nlm_gain(x[i][mu][v], hmap, kl2) * x[i][mu][v];
+                    for (int v = 0; v < 4; ++v) x[i][mu][v] = nlm_gain(x[i][mu][v], fabsf(hmap), kl2, tiny) * x[i][mu][v];
         }
         if constexpr (ONE || TW % 2 == 0) {
 #pragma unroll
