@@ -236,6 +236,38 @@ __device__ __forceinline__ void ising_block_i8(int n, int rep0, int cnt, const i
     }
 }
 
+// Rows of the unit vectors U of quad_block: 128 bytes, and 64 bytes more after
+// every four, so that the four lane groups of a read, four rows apart, touch
+// all banks.
+__device__ __forceinline__ int quad_row(int p) { return p * 16 + (p >> 2) * 8; }
+
+size_t quad_lds_bytes(int n) { return sizeof(double) * (size_t)((n + 15) / 16) * 16 * 18; }
+
+// The quadratic form of quad_block for one replica (u: its first column of U)
+// by one wavefront, lanes owning columns q, pair by pair: an infinite coupling
+// times the dot product of its pair is infinite, while the components' parts of
+// it may have both signs.  NaN if a vector is not finite.
+__device__ __forceinline__ double quad_walk(int n, int d, const void *__restrict__ j, int j_dtype, const double *u) {
+    const int lane = threadIdx.x & 63;
+    bool finite = true;
+    for (int q = lane; q < n; q += 64)
+        for (int mu = 0; mu < d; ++mu) finite = finite && isfinite(u[quad_row(q) + mu]);
+    if (!__all(finite)) return __builtin_nan("");
+    double acc = 0.0;
+#pragma unroll 1
+    for (int q = lane; q < n; q += 64) {
+        double h = 0.0;
+#pragma unroll 1
+        for (int p = 0; p < n; ++p) {
+            double dot = 0.0;
+            for (int mu = 0; mu < d; ++mu) dot = dot + u[quad_row(p) + mu] * u[quad_row(q) + mu];
+            h = h + (double)coupling(j, j_dtype, n, p, q) * dot;
+        }
+        acc += h;
+    }
+    return -wave_sum(acc);
+}
+
 // Quadratic form -sum_{p,q} J_pq u_p . u_q in float64 of cnt replicas of one
 // problem by a block of four wavefronts: the hyperspin energy with the unit
 // vectors u_p = x_p / |x_p| (0 for a zero hyperspin), or, with x = NULL, the
@@ -248,13 +280,6 @@ __device__ __forceinline__ void ising_block_i8(int n, int rep0, int cnt, const i
 // every pair per replica with J read from L2 by every wavefront (N = 100,
 // D = 3, 2000 replicas: 41 us; now 15 us).  Called by all threads of the block;
 // contains block barriers.
-//
-// Rows of U: 128 bytes, and 64 bytes more after every four, so that the four
-// lane groups of a read, four rows apart, touch all banks.
-__device__ __forceinline__ int quad_row(int p) { return p * 16 + (p >> 2) * 8; }
-
-size_t quad_lds_bytes(int n) { return sizeof(double) * (size_t)((n + 15) / 16) * 16 * 18; }
-
 __device__ __forceinline__ void quad_block(int n, int d, int r, int rep0, int cnt, const void *__restrict__ j, int j_dtype,
                            const float *__restrict__ x, const uint64_t *__restrict__ spins, double *__restrict__ out,
                            double *u, double (&red)[4][16]) {
@@ -264,8 +289,7 @@ __device__ __forceinline__ void quad_block(int n, int d, int r, int rep0, int cn
     const int nt = (n + 15) >> 4;
     const int w = (n + 63) >> 6;
     __syncthreads();  // the previous call's reads are done
-    // one thread per hyperspin; q = cnt stands for
-    // the columns without a replica
+    // one thread per hyperspin; q = cnt stands for the columns without a replica
     const int used = cnt * d;
     for (int i = threadIdx.x; i < nt * 16 * (cnt + 1); i += blockDim.x) {
         const int p = i / (cnt + 1), q = i - p * (cnt + 1);
@@ -316,21 +340,32 @@ __device__ __forceinline__ void quad_block(int n, int d, int r, int rep0, int cn
 #pragma unroll
             for (int s = 0; s < 4; ++s) G = __builtin_amdgcn_mfma_f64_16x16x4f64((double)jv[s], ub[16 * s], G, 0, 0, 0);
         }
-        // lane (col, g) of the result holds rows g, g + 4, g + 8, g + 12
+        // lane (col, g) of the result holds rows g, g + 4, g + 8, g + 12; those past n
+        // are left out, 0 times an infinite coupling is not 0
 #pragma unroll
-        for (int v = 0; v < 4; ++v) sum = fma(u[quad_row(16 * I + g + 4 * v) + col], G[v], sum);
+        for (int v = 0; v < 4; ++v) {
+            const int pv = 16 * I + g + 4 * v;
+            sum = pv < n ? fma(u[quad_row(pv) + col], G[v], sum) : sum;
+        }
     }
     sum += __shfl_xor(sum, 16, 64);
     sum += __shfl_xor(sum, 32, 64);
     if (g == 0) red[wv][col] = sum;
     __syncthreads();
-    if (threadIdx.x < (unsigned)cnt) {
+    if (wv == 0) {
         double e = 0.0;
-        for (int mu = 0; mu < d; ++mu) {
-            const int c = threadIdx.x * d + mu;
+        for (int mu = 0; mu < d && lane < cnt; ++mu) {
+            const int c = lane * d + mu;
             e += (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
         }
-        out[rep0 + threadIdx.x] = -e;
+        e = -e;
+        uint64_t redo = d > 1 ? __ballot(e != e) : 0ull;
+        for (; __builtin_expect(redo != 0ull, 0); redo &= redo - 1) {
+            const int q = __ffsll((unsigned long long)redo) - 1;
+            const double v = quad_walk(n, d, j, j_dtype, u + q * d);
+            if (lane == q) e = v;
+        }
+        if (lane < cnt) out[rep0 + lane] = e;
     }
 }
 
