@@ -275,10 +275,12 @@ int team_layout(int tiles, int d, int xs, int js, int64_t blocks, int64_t waves,
     if (!lookup_team(tiles, d, xs, js, true, map)) return kTeamNone;
     const int nc = (tiles + 1) / 2;
     const bool wave = map ? tiles <= kMapMaxTiles : tiles <= resident_tile_limit(d, xs, js);
-    // D = 1, N <= 32: the same work in the same single wavefront. With one state
-    // term blocks of one wavefront are faster than of four (400 steps, 3489
-    // replicas: N = 9 50 against 64 us, N = 32 67 against 70; 16384 replicas: 67
-    // against 62, 65 against 73), with three they are not (66 and 64 us).
+    // D = 1, N <= 32: the same work in the same single wavefront, in blocks of one
+    // or, in the register-resident kernel, of four.  With one state term blocks of
+    // one are faster at every count (400 steps, 4096 replicas: N = 16 36 against 54
+    // us, N = 32 52 against 62; 16384: 38 and 54, 55 and 64; 131072: 135 and 150,
+    // 269 and 285); with three they are no faster where it matters most, N = 32 and
+    // one wavefront per SIMD (104 against 94 us; 87 against 92 below).
     if (nc == 1 && d == 1 && xs == 3 && !map) return kTeamNone;
     if (wave && !map && (nc > 1 || tuned)) {
         const int64_t full = (int64_t)4 * cus;

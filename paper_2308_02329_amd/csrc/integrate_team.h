@@ -128,7 +128,7 @@ __device__ __forceinline__ void integrate_team(const IntegArgs &a, int rep0, bf1
     const int r = a.r;
     const int nt = (n + 15) / 16;
     const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = ONE ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4;
     const int rep = rep0 + (lane & 15) / LPR;
     const int mul = (lane & 15) % LPR;  // packed: the lane's component
@@ -299,7 +299,15 @@ __device__ __forceinline__ void integrate_team(const IntegArgs &a, int rep0, bf1
 #pragma unroll
                 for (int v = 0; v < 4; ++v) x[i][mu][v] = fmaf(ga[mu], acc[i][mu][v], x[i][mu][v]);
         }
-        if (k + 1 < steps) {
+        // A block of one wavefront forms it after the last step too: without the
+        // branch a step is one piece, which the compiler orders as a whole, the
+        // weight's load at its head.  With it the load went to the step's end, and its
+        // time lay on the chain of a step, the more the more blocks a CU had (400
+        // steps, N = 16, bf16, D = 1, 4096 replicas: 40 us with the branch, 36 without;
+        // 16384: 54, 38; D = 4, 512: 74, 48; float32 form, N = 32, D = 3, 512: 128,
+        // 102.  From three wavefronts per SIMD on it gains nothing, N = 32, D = 1,
+        // bf16 loses 7% there: 250, 269 us at 131072).
+        if ((ONE && !MAP) || k + 1 < steps) {
             operand((k + 1) & 1);
             if constexpr (!ONE) __syncthreads();
         }
