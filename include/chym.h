@@ -216,10 +216,11 @@ int chym_map_integrate(const chym_map_problem *prob, const chym_run *run, chym_s
  * pump values x N_r repetitions of the map, all independent (statistics
  * paragraph, Figs. 3-4).  Each problem t is chym_map_integrate(&probs[t],
  * &runs[t]); results are bit-identical to it.  The workspace (device, 256-byte
- * aligned, size from chym_map_batch_workspace_size) receives the task table and
- * the work list of (task, replica block) items, longest run first.  The host tables are copied on `stream`,
- * which is synchronized once before the launches are queued; the launches
- * then run asynchronously.  Calls that share a workspace must not overlap.
+ * aligned, size from chym_map_batch_workspace_size, by the tasks alone)
+ * receives the task table and the work list of (task, replica block) items,
+ * longest run first.  The host tables are copied on `stream`, which is
+ * synchronized once before the launches are queued; the launches then run
+ * asynchronously.  Calls that share a workspace must not overlap.
  * Errors name the offending task; nothing is launched if any task is
  * invalid. */
 int chym_map_batch_workspace_size(const chym_map_problem *probs, const chym_run *runs, int32_t n_tasks,
@@ -280,7 +281,9 @@ typedef struct chym_task {
 
 typedef struct chym_batch chym_batch; /* opaque plan (host object owned by the library) */
 
-/* Device workspace bytes a batch of these tasks (host array) needs. */
+/* Device workspace bytes a batch of these tasks (host array) needs: by the
+ * tasks alone, whatever plans are set and whichever device it runs on (no
+ * device is looked at). */
 int chym_batch_workspace_size(const chym_task *tasks, int32_t n_tasks, size_t *bytes);
 
 /* Validate every task (host array), write the task table and the work list

@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -504,16 +505,59 @@ void assign_branches(const chym_task *tasks, int cus, BatchLayout *L) {
     L->groups.swap(sorted);
 }
 
-int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
+// group key (kind, tiles, d, xs, js): kind 0 resident, 1 streamed-J, 2 sparse rows (one group per d);
+// 3 streamed-J on the packed kernel (one group per shape, all d)
+typedef std::tuple<int, int, int, int, int> GroupKey;
+
+GroupKey group_key(const chym_task &tk) {
+    const Variant v = variant_of(&tk.prob, &tk.run);
+    return v.ell ? GroupKey(2, 0, tk.prob.d, 0, 0) : GroupKey((int)v.slab, v.tiles, tk.prob.d, v.xs, v.js);
+}
+
+int validate_tasks(const chym_task *tasks, int32_t n_tasks) {
     if (n_tasks < 1) return fail(CHYM_EINVAL, "n_tasks = %d must be >= 1", n_tasks);
     if (!tasks) return fail(CHYM_EINVAL, "tasks is NULL");
-    // group key (kind, tiles, d, xs, js): kind 0 resident, 1 streamed-J, 2 sparse rows (one group per d);
-    // 3 streamed-J on the packed kernel (one group per shape, all d)
-    typedef std::tuple<int, int, int, int, int> GroupKey;
-    auto group_of = [&](int t) {
-        const Variant v = variant_of(&tasks[t].prob, &tasks[t].run);
-        return v.ell ? GroupKey(2, 0, tasks[t].prob.d, 0, 0) : GroupKey((int)v.slab, v.tiles, tasks[t].prob.d, v.xs, v.js);
-    };
+    for (int t = 0; t < n_tasks; ++t) {
+        const chym_task &tk = tasks[t];
+        int rc = validate_problem(&tk.prob);
+        if (!rc) rc = validate_run(&tk.run);
+        if (!rc) rc = check_variant(&tk.prob, &tk.run);
+        if (!rc) rc = validate_out(&tk.prob, &tk.run, &tk.out);
+        if (rc) {
+            std::string m = g_err;
+            return fail(rc, "task %d: %s", t, m.c_str());
+        }
+    }
+    return CHYM_OK;
+}
+
+// Work items of a problem's r replicas where blocks take fewest of them.
+size_t most_items(int r, int d) {
+    const int pack = chym::team_block_replicas(chym::kTeamPack, d);
+    return ((size_t)r + pack - 1) / pack;
+}
+
+// Device workspace of a batch, by its (valid) tasks alone: with the most work
+// items (one replica each for sparse rows), groups and staged couplings that a
+// plan or a device gives them.
+size_t batch_bytes(const chym_task *tasks, int32_t n_tasks) {
+    size_t items = 0, staged = 0;
+    std::set<GroupKey> groups;
+    for (int t = 0; t < n_tasks; ++t) {
+        const chym_task &tk = tasks[t];
+        if (tk.run.steps == 0) continue;
+        const Variant v = variant_of(&tk.prob, &tk.run);
+        groups.insert(group_key(tk));
+        items += v.ell ? (size_t)tk.run.r : most_items(tk.run.r, tk.prob.d);
+        staged += align_up(slab_ws_bytes(v));
+    }
+    return batch_tables((size_t)n_tasks, items, groups.size()).off_jf + staged;
+}
+
+int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
+    int rc = validate_tasks(tasks, n_tasks);
+    if (rc) return rc;
+    auto group_of = [&](int t) { return group_key(tasks[t]); };
     struct Load {
         int64_t blocks = 0, waves = 0;  // packed blocks and 16-replica groups of the team integrator
         int team = chym::kTeamNone;
@@ -525,14 +569,6 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
     std::map<GroupKey, std::vector<int2>> by_variant;
     for (int t = 0; t < n_tasks; ++t) {
         const chym_task &tk = tasks[t];
-        int rc = validate_problem(&tk.prob);
-        if (!rc) rc = validate_run(&tk.run);
-        if (!rc) rc = check_variant(&tk.prob, &tk.run);
-        if (!rc) rc = validate_out(&tk.prob, &tk.run, &tk.out);
-        if (rc) {
-            std::string m = g_err;
-            return fail(rc, "task %d: %s", t, m.c_str());
-        }
         if (tk.run.steps == 0) continue;
         if (variant_of(&tk.prob, &tk.run).ell) {
             ell_replicas += tk.run.r;
@@ -824,18 +860,23 @@ struct MapGroup {
     int tiles, d, xs, team, item_off, n_items;  // team: layout of the team integrator
 };
 
+typedef std::tuple<int, int, int> MapVariant;  // (tiles, d, xs)
+
 struct MapBatchLayout {
     std::vector<chym::IntegArgs> args;
+    std::vector<MapVariant> variants;  // of the tasks
     std::vector<int2> items;  // (task, replica block), grouped by variant, longest task first
     std::vector<MapGroup> groups;
     size_t off_tasks, off_items, total;
 };
 
-int map_batch_layout(const chym_map_problem *probs, const chym_run *runs, int32_t n_tasks, MapBatchLayout *L) {
+// Validates the tasks, fills their kernel arguments and sizes the workspace, by
+// the tasks alone: with the most work items that a device gives them.
+int map_batch_args(const chym_map_problem *probs, const chym_run *runs, int32_t n_tasks, MapBatchLayout *L) {
     if (n_tasks < 1) return fail(CHYM_EINVAL, "n_tasks = %d must be >= 1", n_tasks);
     if (!probs || !runs) return fail(CHYM_EINVAL, "problems or runs is NULL");
-    std::map<std::tuple<int, int, int>, std::vector<int>> by_variant;  // (tiles, d, xs): tasks
     L->args.resize(n_tasks);
+    L->variants.resize(n_tasks);
     for (int t = 0; t < n_tasks; ++t) {
         MapTask mt;
         int rc = map_setup(&probs[t], &runs[t], &mt);
@@ -844,8 +885,25 @@ int map_batch_layout(const chym_map_problem *probs, const chym_run *runs, int32_
             return fail(rc, "task %d: %s", t, m.c_str());
         }
         L->args[t] = mt.a;
-        if (runs[t].steps > 0) by_variant[std::make_tuple(mt.tiles, probs[t].d, mt.xs)].push_back(t);
+        L->variants[t] = std::make_tuple(mt.tiles, probs[t].d, mt.xs);
     }
+    size_t items = 0;
+    for (int t = 0; t < n_tasks; ++t)
+        if (runs[t].steps > 0) items += most_items(runs[t].r, probs[t].d);
+    L->off_tasks = 0;
+    L->off_items = align_up(sizeof(chym::IntegArgs) * (size_t)n_tasks);
+    // and an unused third area: a workspace was never less than three
+    L->total = L->off_items + align_up(sizeof(int2) * std::max<size_t>(1, items)) + kAlign;
+    return CHYM_OK;
+}
+
+// The groups and work items for the current device.
+int map_batch_layout(const chym_map_problem *probs, const chym_run *runs, int32_t n_tasks, MapBatchLayout *L) {
+    int rc = map_batch_args(probs, runs, n_tasks, L);
+    if (rc) return rc;
+    std::map<MapVariant, std::vector<int>> by_variant;
+    for (int t = 0; t < n_tasks; ++t)
+        if (runs[t].steps > 0) by_variant[L->variants[t]].push_back(t);
     L->items.clear();
     L->groups.clear();
     const int cus = current_cus();
@@ -868,10 +926,6 @@ int map_batch_layout(const chym_map_problem *probs, const chym_run *runs, int32_
         g.n_items = (int)L->items.size() - g.item_off;
         L->groups.push_back(g);
     }
-    L->off_tasks = 0;
-    L->off_items = align_up(sizeof(chym::IntegArgs) * (size_t)n_tasks);
-    // and an unused third area: a workspace was never less than three
-    L->total = L->off_items + align_up(sizeof(int2) * std::max<size_t>(1, L->items.size())) + kAlign;
     return CHYM_OK;
 }
 
@@ -892,7 +946,8 @@ int batch_build(const chym_task *tasks, int32_t n_tasks, void *workspace, size_t
     if (rc) return rc;
     if (!workspace) return fail(CHYM_EINVAL, "workspace is NULL");
     if ((uintptr_t)workspace % kAlign) return fail(CHYM_EINVAL, "workspace must be %zu-byte aligned", kAlign);
-    if (ws_bytes < L.total) return fail(CHYM_ENOMEM, "workspace has %zu bytes, %zu needed", ws_bytes, L.total);
+    const size_t need = std::max(L.total, batch_bytes(tasks, n_tasks));
+    if (ws_bytes < need) return fail(CHYM_ENOMEM, "workspace has %zu bytes, %zu needed", ws_bytes, need);
     rc = check_device();
     if (rc) return rc;
     chym_batch *b = new (std::nothrow) chym_batch;
@@ -1053,7 +1108,7 @@ int chym_map_batch_workspace_size(const chym_map_problem *probs, const chym_run 
     if (!bytes) return fail(CHYM_EINVAL, "bytes is NULL");
     *bytes = 0;
     MapBatchLayout L;
-    int rc = map_batch_layout(probs, runs, n_tasks, &L);
+    int rc = map_batch_args(probs, runs, n_tasks, &L);
     if (rc) return rc;
     *bytes = L.total;
     return CHYM_OK;
@@ -1233,10 +1288,9 @@ int chym_integrate_ws(const chym_problem *prob, const chym_run *run, void *works
 
 int chym_batch_workspace_size(const chym_task *tasks, int32_t n_tasks, size_t *bytes) {
     if (!bytes) return fail(CHYM_EINVAL, "bytes is NULL");
-    BatchLayout L;
-    int rc = plan_layout(tasks, n_tasks, &L);
+    int rc = validate_tasks(tasks, n_tasks);
     if (rc) return rc;
-    *bytes = L.total;
+    *bytes = batch_bytes(tasks, n_tasks);
     return CHYM_OK;
 }
 
@@ -1334,10 +1388,10 @@ ProbeLayout probe_layout(int n, int d, int r, int steps) {
     L.off_x = L.off_pump + align_up((size_t)r * 4);
     L.off_alpha = L.off_x + align_up((size_t)n * r * d * 4);
     L.off_batch = L.off_alpha + align_up((size_t)steps * d * 4);
-    // batch workspace of one task: its work list is largest with 16-replica
-    // items; the staged couplings of a streamed-J task follow the tables
-    // (sized for three coupling terms, the most any form stages)
-    L.batch_bytes = batch_tables(1, (size_t)((r + 15) / 16), 1).off_jf + align_up(chym::slab_jfrag_bytes((n + 15) / 16, 3));
+    // batch workspace of one task, as batch_bytes has it; the staged couplings of
+    // a streamed-J task follow the tables (sized for three coupling terms, the
+    // most any form stages)
+    L.batch_bytes = batch_tables(1, most_items(r, d), 1).off_jf + align_up(chym::slab_jfrag_bytes((n + 15) / 16, 3));
     L.total = L.off_batch + L.batch_bytes;
     return L;
 }
