@@ -463,20 +463,16 @@ int validate_out(const chym_problem *prob, const chym_run *run, const chym_out *
 // in turn, whatever the groups take.  So the graph has kBranches branches, and
 // the groups go to the one that is free first, longest first, by a rough time:
 // that of all its items, one at a time on every compute unit, or of its longest
-// item.  A step of an item, in us, from what was measured at N = 100 to 800:
-// 0.3 + 1e-3 n (sparse), + 2.2e-5 n^2 (slab), + 1e-5 n^2 (the other dense ones),
-// twice and four times that for three state terms with one and three coupling
-// terms.  150 mixed solves of 32 runs: 5.0 ms with a branch per group and a
+// item.  150 mixed solves of 32 runs: 5.0 ms with a branch per group and a
 // packed streamed-J group per size and D, 2.8 ms now (2.5 ms of it the one such
 // group of N = 800); 10 000 such solves of 5000 steps, tuned: 1.02 s, 1.16 s
 // one group after another.
 constexpr int kBranches = 4;
 
-double item_time(const Group &g, const chym_task &tk) {
-    const double n = tk.prob.n;
-    if (g.v.ell) return tk.run.steps * (0.3 + 1e-3 * n);
-    const double terms = g.v.js == 3 ? 4.0 : g.v.xs == 3 ? 2.0 : 1.0;
-    return tk.run.steps * (0.3 + terms * (g.v.slab && !g.spack ? 2.2e-5 : 1e-5) * n * n);
+double item_time(const Group &g, const chym_task &tk, const int2 &item) {
+    const bool slab = g.v.slab && !g.spack && g.team == chym::kTeamNone;
+    return tk.run.steps * (g.v.ell ? chym::sparse_step_us(tk.prob.n, item.y & 7)
+                                   : chym::dense_step_us(tk.prob.n, g.v.xs, g.v.js, slab));
 }
 
 void assign_branches(const chym_task *tasks, int cus, BatchLayout *L) {
@@ -485,7 +481,8 @@ void assign_branches(const chym_task *tasks, int cus, BatchLayout *L) {
         const Group &g = L->groups[gi];
         double longest = 0.0, all = 0.0;
         for (int i = 0; i < g.n_items; ++i) {
-            const double t = item_time(g, tasks[L->items[g.item_off + i].x]);
+            const int2 &it = L->items[g.item_off + i];
+            const double t = item_time(g, tasks[it.x], it);
             longest = std::max(longest, t);
             all += t / cus;
         }

@@ -222,6 +222,9 @@ constexpr int kTeamPlane = 2;  // 16 replicas x d planes per block
 int team_layout(int tiles, int d, int xs, int js, int64_t blocks, int64_t waves, bool map, bool tuned, int cus);
 // Replicas per block of a layout (0 for kTeamNone).
 int team_block_replicas(int layout, int d);
+// Rough time of one step of a batch's item, in us.
+double dense_step_us(int n, int xs, int js, bool slab);
+double sparse_step_us(int n, int lrb);
 // One problem (items = NULL, `blocks` of its replica blocks), or n blocks'
 // items (task, replica block) of many problems of one shape.
 hipError_t launch_integrate_team(int layout, int tiles, int d, int xs, int js, bool map, int blocks,

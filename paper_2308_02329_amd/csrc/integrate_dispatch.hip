@@ -294,6 +294,20 @@ int team_layout(int tiles, int d, int xs, int js, int64_t blocks, int64_t waves,
     return plane && (nc == 1 || d == 3 || xs == 1) ? kTeamPlane : kTeamPack;
 }
 
+// From what was measured at N = 100 to 800: 0.3 us, and 2.2e-5 n^2 on the slab
+// kernel, 1e-5 n^2 on the other dense ones, twice and four times that for three
+// state terms with one and three coupling terms.
+double dense_step_us(int n, int xs, int js, bool slab) {
+    const double terms = js == 3 ? 4.0 : xs == 3 ? 2.0 : 1.0;
+    return 0.3 + terms * (slab ? 2.2e-5 : 1e-5) * n * n;
+}
+
+// The gather integrator's step goes with the block's units, n for each of its
+// 2^lrb replicas (N = 800, four replicas 0.9 us, N = 200, D = 1, two 0.23 us).
+// Measured on 3-regular rows: the width of a task's rows lies in its couplings,
+// in device memory, and wide rows take longer (20% rows at N = 200: 13 us).
+double sparse_step_us(int n, int lrb) { return 0.2 + 2.5e-4 * ((int64_t)n << lrb); }
+
 int team_block_replicas(int layout, int d) { return layout == kTeamNone ? 0 : team_replicas(d, layout == kTeamPack); }
 
 hipError_t launch_integrate_team(int layout, int tiles, int d, int xs, int js, bool map, int blocks,
