@@ -256,21 +256,21 @@ static TeamFn lookup_team(int tiles, int d, int xs, int js, bool pack, bool map)
 //   N = 200, D = 3, bf16   1024: packed 0.63, plane 1.09, slab 1.44
 //                          20000: 11.6, 6.1, 8.2
 // Packed blocks have the shortest step, and are the fastest up to two of them
-// on a CU (four with two chunks, eight with one, and twice as many for the
-// map, whose steps hold more vector work).  Beyond that the plane layout is
-// faster where the packed one idles a column (D = 3) or where the quad sums
-// weigh more than the operand exchange (bf16); otherwise packed blocks stay
-// level with it.  Against one wavefront per 16 replicas both lose once those
-// fill the SIMDs: the wave's time goes up in steps of 16384 replicas, the
-// team's in proportion, so the line is drawn at 0.9 of a full step (0.7 with
-// three wavefronts on four SIMDs; 0.6 of the first against a tuned plan, which
-// overlaps two or three wavefronts per SIMD at full load).  The map takes the team at every size: the
-// medium's gain is vector work, which one wavefront per SIMD cannot overlap
-// with its products (N = 100, D = 3, 65536 replicas: 28.2 us a step, plane
-// 23.4).  Against the streamed-J kernel both layouts win at every replica
-// count, except where no plane layout is built (its operand does not fit LDS
-// twice: float32 at D = 4 beyond 12 tiles) and J is one term: there packed
-// blocks are 5-10% slower beyond two to a CU.
+// on a CU (four with two chunks, eight with one, and twice as many for the map,
+// whose steps hold more vector work).  Beyond that the plane layout is faster
+// where the packed one idles a column (D = 3) or where the quad sums weigh more
+// than the operand exchange (bf16); otherwise packed blocks stay level with it,
+// and no plane kernel is built.  Against one wavefront per 16 replicas both
+// lose once those fill the SIMDs: the wave's time goes up in steps of 16384
+// replicas, the team's in proportion, so the line is drawn at 0.9 of a full
+// step (0.7 with three wavefronts on four SIMDs; 0.6 of the first against a
+// tuned plan, which overlaps two or three wavefronts per SIMD at full load).
+// The map takes the team at every size: the medium's gain is vector work, which
+// one wavefront per SIMD cannot overlap with its products (N = 100, D = 3,
+// 65536 replicas: 28.2 us a step, plane 23.4).  Against the streamed-J kernel
+// both layouts win at every replica count, except where the plane layout's
+// operand does not fit LDS twice (float32 at D = 4 beyond 12 tiles) and J is
+// one term: there packed blocks are 5-10% slower beyond two to a CU.
 int team_layout(int tiles, int d, int xs, int js, int64_t blocks, int64_t waves, bool map, bool tuned, int cus) {
     if (!lookup_team(tiles, d, xs, js, true, map)) return kTeamNone;
     const int nc = (tiles + 1) / 2;
@@ -287,11 +287,10 @@ int team_layout(int tiles, int d, int xs, int js, int64_t blocks, int64_t waves,
         const int64_t steps = tuned ? 1 : (waves + full - 1) / full;
         if (10 * waves > (tuned ? 6 : nc == 3 ? 7 : 9) * steps * full) return kTeamNone;
     }
-    const bool plane = lookup_team(tiles, d, xs, js, false, map) != nullptr;
     const int64_t per_cu = (blocks + cus - 1) / cus;
     if (per_cu <= (nc == 1 ? 8 : nc == 2 ? 4 : 2) * (map ? 2 : 1)) return kTeamPack;
-    if (!wave && !plane && d > 1 && js == 1) return kTeamNone;
-    return plane && (nc == 1 || d == 3 || xs == 1) ? kTeamPlane : kTeamPack;
+    if (!wave && js == 1 && team_lds_bytes(nc, d, xs, false) > kSlabMaxLds) return kTeamNone;
+    return lookup_team(tiles, d, xs, js, false, map) ? kTeamPlane : kTeamPack;
 }
 
 // From what was measured at N = 100 to 800: 0.3 us, and 2.2e-5 n^2 on the slab

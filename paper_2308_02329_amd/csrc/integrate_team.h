@@ -328,7 +328,13 @@ __device__ __forceinline__ void integrate_team(const IntegArgs &a, int rep0, bf1
 // Wavefronts per SIMD the registers are limited for: an estimate of what the
 // step loop holds (J fragments, state and accumulators, the operand fragments
 // read ahead), rounded down to a budget of 512 / WPE registers; two at least,
-// which also keeps the accumulators in ordinary registers.
+// which also keeps the accumulators in ordinary registers.  Six variants hold
+// more than their budget and spill: 2, 24 and 40 registers with float couplings
+// at D = 3 (plane, NC = 6 to 8), 6 at D = 2 (plane, one state term, NC = 8) and 4
+// in the packed layout with one state term, NC = 6, D = 2 to 4.  They are faster
+// than the streamed-J kernel all the same (200 steps, 4096 replicas: float
+// couplings, D = 3, N = 192 815 against 1074 us, N = 256 1290 against 1440; one
+// state term, N = 190, D = 4 282 against 293).
 template <int D, int XS, int JS, int NC, int TW, bool PACK>
 constexpr int team_wpe() {
     constexpr int P = PACK ? 1 : D;
@@ -357,11 +363,13 @@ constexpr int kTeamMaxTiles = 16;
 typedef void (*TeamFn)(IntegArgs, int, const IntegArgs *, const int2 *);
 
 // The plane layout's operand of all D components must fit LDS twice; D = 1
-// has the packed layout only (they coincide).
+// has the packed layout only (they coincide), and so have three state terms with
+// D = 2 and 4 beyond one chunk, where team_layout never takes the other.
 template <int D, int XS, int JS, int NC, int TW, bool MAP, bool PACK>
 constexpr TeamFn team_fn() {
     if constexpr (MAP && (JS != 1 || 2 * NC > kMapMaxTiles + 1)) return nullptr;
-    else if constexpr (!PACK && (D == 1 || team_lds_bytes(NC, D, XS, false) > kSlabMaxLds)) return nullptr;
+    else if constexpr (!PACK && (D == 1 || (XS == 3 && D != 3 && NC > 1) || team_lds_bytes(NC, D, XS, false) > kSlabMaxLds))
+        return nullptr;
     else return k_integrate_team<D, XS, JS, NC, TW, PACK, MAP>;
 }
 
