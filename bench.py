@@ -53,14 +53,20 @@ PRECISION_TRAFFIC_SOURCE = ("profiles/hbm_traffic_slab_n1000_d4.md: rocprofv3 --
                             "not measured in this run")
 
 
-def kernel_name(tiles, d, precision, plan):
+def kernel_name(tiles, d, precision, plan, replicas, tuned):
+    """The integrator of a batch of this shape with `replicas` runs in all: the
+    plan's kernel where they fill the chip (1024 SIMDs of 16 replicas; a tuned
+    plan from 60% on, the default one from 90%), else the team integrator."""
     xs = 3 if precision == "f32" else 1
     kind = plan.get("kernel")
-    if kind == 2:
-        return f"k_integrate_persistent_lds<{tiles}, {d}, {xs}, 1, 2>"
-    if kind == 3:
-        return f"k_integrate_persistent_lds<{tiles}, {d}, {xs}, 1, 1>"
-    return f"k_integrate_persistent<{tiles}, {d}, {xs}, 1>"
+    if replicas < (0.6 if tuned else 0.9) * 16384 and kind != 5:
+        return "k_integrate_team (rows of a problem over the wavefronts of a block)"
+    if kind == 5:
+        return "k_integrate_slab, k_integrate_spack or k_integrate_team (streamed-J sizes, by fill)"
+    lds = {2: 2, 3: 1, 6: 3}.get(kind)
+    if lds:
+        return f"k_integrate_persistent_lds<{tiles}, {d}, {xs}, 1, {lds}>"
+    return f"k_integrate_persistent{'_pipe' if kind == 4 else ''}<{tiles}, {d}, {xs}, 1>"
 
 
 def parse():
@@ -474,7 +480,7 @@ def run_map(args, torch, api, synth):
                        "n": n, "d": d, "replicas": R, "round_trips": steps, "precision": "f32"},
             "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                          "frac": achieved / PEAK_BF16_TFLOPS, "traffic": None,
-                         "kernel": "k_integrate_team<3, 3, 1, 4, 2, false, true> (plane layout)", "kernel_ms": kms}}
+                         "kernel": "k_integrate_team<3, 3, 1, 4, 2, false, true, 2> (plane layout)", "kernel_ms": kms}}
 
 
 def run_sparse(args, torch, api, synth):
@@ -589,7 +595,7 @@ def run_stats(args, torch, api, synth):
                        "round_trips": steps, "precision": "f32"},
             "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                          "frac": achieved / PEAK_BF16_TFLOPS, "traffic": None,
-                         "kernel": "k_integrate_team<1, 3, 1, 4, 2, true, true>", "kernel_ms": ms1},
+                         "kernel": "k_integrate_team<1, 3, 1, 4, 2, true, true, 3>", "kernel_ms": ms1},
             "map_batch_ms": {"d1": ms1, "d2": kms[2] / args.steps}}
 
 
@@ -648,7 +654,7 @@ def run_xy(args, torch, api, synth):
                        "n": n, "graphs": n_graphs, "runs": runs, "round_trips": steps, "precision": "f32"},
             "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                          "frac": achieved / PEAK_BF16_TFLOPS, "traffic": None,
-                         "kernel": "k_integrate_team<2, 3, 1, 4, 2, true, true>", "kernel_ms": ms}}
+                         "kernel": "k_integrate_team<2, 3, 1, 4, 2, true, true, 3>", "kernel_ms": ms}}
 
 
 def main():
@@ -724,7 +730,8 @@ def main():
     avg_s = kern_ms[dk] / args.steps / 1e3
     achieved = flops_k / avg_s / 1e12
     plan = api.chym_plan_get(args.n, dk, args.precision, torch.int8)
-    kname = kernel_name((n + 15) // 16, dk, args.precision, plan)
+    kname = kernel_name((n + 15) // 16, dk, args.precision, plan, args.instances * R,
+                        bool(args.plan_cache or args.autotune))
     roof = {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_BF16_TFLOPS, "traffic": TRAFFIC.get((kname, args.n, args.instances, R)),
             "traffic_source": TRAFFIC_SOURCE if (kname, args.n, args.instances, R) in TRAFFIC else None,

@@ -142,7 +142,7 @@ const char *chym_last_error(void);
  * steps - 1.  Splitting a run into calls with consecutive start_step gives
  * bit-identical results to one call.
  *
- * Three integrators, chosen by size and replica count, give identical results
+ * Four integrators, chosen by size and replica count, give identical results
  * for the same problem: a register-resident one (no workspace) up to n = 192 (d = 1),
  * 144/160 (d = 2, float32/bf16 form), 128 (d = 3), 112 (d = 4), or less
  * for float J in the float32 form; and a streamed-J one for larger n, up to
@@ -154,8 +154,10 @@ const char *chym_last_error(void);
  * times per step, with the same results.  Up to n = 256, launches whose
  * replicas do not fill the chip on these (and most beyond the
  * register-resident sizes) run on the team integrator, which spreads a
- * problem's rows over the wavefronts of a block; the sizes that need a
- * workspace need it all the same.  chym_integrate returns
+ * problem's rows over the wavefronts of a block; beyond, launches of few
+ * replicas (up to one block of 16, 8, 4, 4 replicas for d = 1..4 per compute
+ * unit, three in some float32 forms) on the packed streamed-J integrator.  The
+ * sizes that need a workspace need it all the same.  chym_integrate returns
  * CHYM_EUNSUPPORTED where a workspace is needed. */
 int chym_integrate(const chym_problem *prob, const chym_run *run, chym_stream_t stream);
 
@@ -192,9 +194,10 @@ int chym_integrate_noalloc(const chym_problem *prob, const chym_run *run, chym_s
  * J holds the coupling pattern (e.g. +-1); jmag is the coupling magnitude J.
  * run->pump holds h per replica (absolute, not normalized), run->x the
  * amplitudes A [n][r][d] (in/out), run->dt must be 1 (one round trip per
- * step), run->alpha the annealing table as for chym_integrate.  N <= 112
- * (register-resident integrator); couplings must be exact in one bf16 term
- * (CHYM_J_I8, CHYM_J_BF16, CHYM_J_FP8); otherwise CHYM_EUNSUPPORTED. */
+ * step), run->alpha the annealing table as for chym_integrate.  h may be 0 or
+ * negative (an undriven or an absorbing medium).  N <= 112; couplings must be
+ * exact in one bf16 term (CHYM_J_I8, CHYM_J_BF16, CHYM_J_FP8); otherwise
+ * CHYM_EUNSUPPORTED. */
 typedef struct chym_map_problem {
     int32_t n;        /* parametric-oscillator blocks (hyperspins) N >= 1 */
     int32_t d;        /* components per hyperspin, 1 <= D <= 4 */
@@ -437,13 +440,17 @@ int chym_to_bf16(const float *src, uint16_t *dst, int32_t n, chym_stream_t strea
  * The table is process-wide and starts empty: CHYM_KERNEL_REGJ with 4 waves
  * per block for the register-resident variants, CHYM_KERNEL_SLAB with 16
  * waves up to 32 row tiles where built and 8 beyond for the streamed-J ones.
- * Launches that leave the chip idle on these (few replicas in all tasks of a
- * variant), and most streamed-J variants up to n = 256, run on the team
- * integrator (rows of a problem over the wavefronts of a block) instead,
- * unless chym_plan_set chose the kernel: entries of the autotuner and of plan
- * files were measured with the chip full.
+ * Which entries bind: chym_plan_set's always.  Those of the autotuner and of
+ * plan files were measured with the chip full, and give way, like the default,
+ * where it is not: to the team integrator up to n = 256 (register-resident
+ * variants below 60% of the chip's 16-replica wavefronts; most streamed-J ones
+ * at every replica count, where it was faster throughout) and to the packed
+ * streamed-J integrator beyond (at most one of its blocks per compute unit).
+ * Neither is a plan kind, and the autotuner does not time them: for those
+ * launches chym_plan_get reports an entry that does not run.
  * The single-problem calls (chym_integrate_ws, chym_solve_ws) use the
- * streamed-J entries too.  Plans change speed only, never results.
+ * streamed-J entries too, by the same rule; they read no register-resident
+ * ones.  Plans change speed only, never results.
  */
 #define CHYM_KERNEL_AUTO 0
 #define CHYM_KERNEL_REGJ 1
@@ -472,8 +479,8 @@ typedef struct chym_plan_entry {
 /* Install (or, with CHYM_KERNEL_AUTO, remove) a plan entry. */
 int chym_plan_set(const chym_plan_entry *entry);
 
-/* The entry the batched path will use for this problem shape (the default
- * when none was set). */
+/* The entry of this problem shape (the default when none was set), which the
+ * batched path uses unless the launch gives way as above. */
 int chym_plan_get(int32_t n, int32_t d, int32_t precision, int32_t j_dtype, chym_plan_entry *entry);
 
 /* Device workspace bytes chym_plan_autotune needs for `replicas` replicas. */

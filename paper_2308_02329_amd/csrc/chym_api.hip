@@ -933,7 +933,7 @@ namespace {
 // Validates the tasks, writes the task table and the work list into the
 // caller's workspace (copies on `upload`, which is then synchronized, so the
 // host tables may go away) and, when `want_graph` is set, records the launch
-// sequence as a HIP graph with one branch per variant group.
+// sequence as a HIP graph with up to kBranches branches of groups.
 int batch_build(const chym_task *tasks, int32_t n_tasks, void *workspace, size_t ws_bytes, bool want_graph,
                 hipStream_t upload, chym_batch **plan) {
     if (!plan) return fail(CHYM_EINVAL, "plan is NULL");

@@ -462,8 +462,8 @@ __global__ __launch_bounds__(256) void k_gather_replicas(int n, int d, int r_src
 
 hipError_t launch_features(int n, int d, int r, const void *j, int j_dtype, const float *x, uint64_t *prev,
                            float *feat, int feat_stride, int feat_off, hipStream_t stream) {
-    // 32 replicas per block while their first components leave room for two
-    // blocks on a CU or fit at all, then 16, then one replica per wavefront
+    // 32 replicas per block while their first components fit LDS (n <= 1120), then
+    // 16 (n <= 2400), then one replica per wavefront
     constexpr size_t kMax = 159 * 1024;
     if (feat_lds(n, 16) > kMax) {
         hipLaunchKernelGGL(k_features_one, dim3(r), dim3(64), sizeof(float) * 2 * (size_t)n, stream, n, d, r, j, j_dtype,

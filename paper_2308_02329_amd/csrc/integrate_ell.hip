@@ -327,8 +327,8 @@ __global__ __launch_bounds__(kEllThreads) void k_integrate_ell(IntegArgs a, int 
     ell_run<D>(a, blockIdx.x, lrb, row_budget, sm);
 }
 
-// Many problems of one D: blocks pop items, (task, replica block and block
-// size: ell_item), from the counter (zero at launch) until n_items are taken.
+// Many problems of one D: blocks pop items, (task, 8 x replica block + log2 of
+// its replicas), from the counter (zero at launch) until n_items are taken.
 template <int D>
 __global__ __launch_bounds__(kEllThreads) void k_integrate_ell_persistent(const IntegArgs *__restrict__ tasks,
                                                                           const int2 *__restrict__ items,

@@ -14,8 +14,8 @@ namespace chym {
 // components are read by consecutive lanes and 16 rows are in flight; its 16
 // bits go to LDS, where four make a spin word.  One thread per replica walked
 // the rows one after the other and was bound by their latency (N = 200, D = 3,
-// 20000 replicas: 120 us; now 33 us, 1.5 TB/s; N = 100, 2000 replicas: 59 and
-// 6.7).  Called by all threads of the block; contains block barriers.
+// 20000 replicas: 120 us; now 12 us, 3.9 TB/s; N = 100, 2000 replicas: 59 and
+// 5.6).  Called by all threads of the block; contains block barriers.
 struct ReadoutLds {
     uint16_t bits[16][64];
     float share[16][64];
@@ -185,7 +185,7 @@ __device__ __forceinline__ i32x4 int8_row16(const int8_t *__restrict__ J, int n,
 // multiplies its rows of G by their spins, and the sums meet in LDS.  All
 // integer, so any order gives the same energy.  The per-replica walk over the
 // rows that this replaces was bound by its chain of row reads (N = 200, 20000
-// replicas: 180 us; now 16 us).  Called by all threads of the block; contains
+// replicas: 180 us; now 12 us).  Called by all threads of the block; contains
 // block barriers.
 __device__ __forceinline__ void ising_block_i8(int n, int rep0, int cnt, const int8_t *__restrict__ J,
                                const uint64_t *__restrict__ spins, int32_t *__restrict__ e_i32,
@@ -278,7 +278,7 @@ __device__ __forceinline__ double quad_walk(int n, int d, const void *__restrict
 // 4 g + u, and reads U in the same order; wavefront w takes row tiles w, w+4,
 // ....  The float64 vector code that this replaces formed the dot products of
 // every pair per replica with J read from L2 by every wavefront (N = 100,
-// D = 3, 2000 replicas: 41 us; now 15 us).  Called by all threads of the block;
+// D = 3, 2000 replicas: 41 us; now 14 us).  Called by all threads of the block;
 // contains block barriers.
 __device__ __forceinline__ void quad_block(int n, int d, int r, int rep0, int cnt, const void *__restrict__ j, int j_dtype,
                            const float *__restrict__ x, const uint64_t *__restrict__ spins, double *__restrict__ out,
