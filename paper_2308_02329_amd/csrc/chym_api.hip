@@ -560,6 +560,7 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         int team = chym::kTeamNone;
         bool spack = false;
         bool narrow = true;  // all couplings in eight bits
+        PlanValue plan{};    // read once: the items and the launch are both by it
     };
     std::map<GroupKey, Load> load;
     int64_t ell_replicas = 0;  // of all sparse tasks
@@ -581,7 +582,7 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
     for (auto &kv : load) {
         const int tiles = std::get<1>(kv.first), d = std::get<2>(kv.first), xs = std::get<3>(kv.first);
         const int js = std::get<4>(kv.first);
-        const PlanValue pv = plan_for(std::make_tuple(tiles, d, xs, js));
+        const PlanValue pv = kv.second.plan = plan_for(std::make_tuple(tiles, d, xs, js));
         if (pv.from != PlanValue::kSet)
             kv.second.team = chym::team_layout(tiles, d, xs, js, kv.second.blocks, kv.second.waves, false,
                                                pv.from == PlanValue::kTuned, cus);
@@ -607,7 +608,7 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
         } else if (load[gk].spack) {
             slab = chym::team_block_replicas(chym::kTeamPack, tk.prob.d);
         } else if (!v.slab) {
-            const PlanValue pv = plan_for(key_of(v, tk.prob.d));
+            const PlanValue &pv = load[gk].plan;
             slab = pv.kind != chym::kKernelRegJ ? 16 * pv.waves : 16;
         }
         const int slabs = (tk.run.r + slab - 1) / slab;
@@ -649,10 +650,10 @@ int plan_layout(const chym_task *tasks, int32_t n_tasks, BatchLayout *L) {
             for (const int2 &it : lst) g.lds = std::max(g.lds, chym::ell_lds_bytes(tasks[it.x].prob.n, g.d, it.y & 7));
         } else if (g.v.slab) {
             g.kind = -1;
-            g.waves = plan_for(key_of(g.v, g.d)).waves;  // the slab kernel's block size
+            g.waves = load[kv.first].plan.waves;  // the slab kernel's block size
             g.lds = chym::slab_lds_bytes(g.v.tiles, g.d, g.v.xs);
         } else {
-            const PlanValue pv = plan_for(key_of(g.v, g.d));
+            const PlanValue &pv = load[kv.first].plan;
             g.kind = pv.kind;
             g.waves = pv.kind != chym::kKernelRegJ ? pv.waves : kPersistentWaves;
         }
