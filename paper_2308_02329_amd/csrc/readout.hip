@@ -383,14 +383,14 @@ __global__ __launch_bounds__(kEnergyThreads) void k_ising_energy_i8(int n, int r
     ising_block_i8(n, rep0, min(16, r - rep0), J, spins, e_i32, e_f64, red);
 }
 
-__global__ __launch_bounds__(kEnergyThreads) void k_quad(int n, int d, int r, const void *__restrict__ j, int j_dtype,
+__global__ __launch_bounds__(kEnergyThreads) void k_quad(int n, int d, int r, int first, const void *__restrict__ j, int j_dtype,
                                                          const float *__restrict__ x,
                                                          const uint64_t *__restrict__ spins,
                                                          double *__restrict__ out) {
     extern __shared__ double u[];
     __shared__ double red[4][16];
     const int rp = 16 / d;
-    const int rep0 = blockIdx.x * rp;
+    const int rep0 = first + blockIdx.x * rp;
     quad_block(n, d, r, rep0, min(rp, r - rep0), j, j_dtype, x, spins, out, u, red);
 }
 
@@ -628,6 +628,19 @@ static hipError_t allow_lds(F fn, size_t lds) {
     return hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
+static hipError_t launch_quad(int n, int d, int r, const void *j, int j_dtype, const float *x, const uint64_t *spins,
+                              double *out, hipStream_t stream) {
+    const size_t lds = quad_lds_bytes(n);
+    hipError_t e = allow_lds(k_quad, lds);
+    if (e != hipSuccess) return e;
+    const int rp = 16 / d;
+    const int64_t blocks = ((int64_t)r + rp - 1) / rp;
+    for (int64_t b = 0; b < blocks; b += max_blocks(kEnergyThreads))
+        hipLaunchKernelGGL(k_quad, dim3((unsigned)std::min<int64_t>(blocks - b, max_blocks(kEnergyThreads))),
+                           dim3(kEnergyThreads), lds, stream, n, d, r, (int)(b * rp), j, j_dtype, x, spins, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_ising_energy(int n, int r, const void *j, int j_dtype, const uint64_t *spins, int32_t *e_i32,
                                double *e_f64, hipStream_t stream) {
     if (j_dtype == CHYM_J_I8) {
@@ -640,11 +653,7 @@ hipError_t launch_ising_energy(int n, int r, const void *j, int j_dtype, const u
             if (k == r - r0) break;  // r0 + part may pass the largest int
         }
     } else if (quad_takes(n, j_dtype)) {
-        const size_t lds = quad_lds_bytes(n);
-        hipError_t e = allow_lds(k_quad, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_quad, dim3((r + 15) / 16), dim3(kEnergyThreads), lds, stream, n, 1, r, j, j_dtype,
-                           (const float *)nullptr, spins, e_f64);
+        return launch_quad(n, 1, r, j, j_dtype, nullptr, spins, e_f64, stream);
     } else {
         const int waves = kEnergyThreads / 64;
         hipLaunchKernelGGL(k_ising_energy, dim3((r + waves - 1) / waves), dim3(kEnergyThreads), 0, stream, n, r, j,
@@ -655,15 +664,7 @@ hipError_t launch_ising_energy(int n, int r, const void *j, int j_dtype, const u
 
 hipError_t launch_hs_energy(int n, int d, int r, const void *j, int j_dtype, const float *x, double *e_hs,
                             hipStream_t stream) {
-    if (quad_takes(n, j_dtype)) {
-        const size_t lds = quad_lds_bytes(n);
-        hipError_t e = allow_lds(k_quad, lds);
-        if (e != hipSuccess) return e;
-        const int rp = 16 / d;
-        hipLaunchKernelGGL(k_quad, dim3((r + rp - 1) / rp), dim3(kEnergyThreads), lds, stream, n, d, r, j, j_dtype, x,
-                           (const uint64_t *)nullptr, e_hs);
-        return hipGetLastError();
-    }
+    if (quad_takes(n, j_dtype)) return launch_quad(n, d, r, j, j_dtype, x, nullptr, e_hs, stream);
     const size_t lds = sizeof(double) * (size_t)n * d;
     if (j_dtype == CHYM_J_I8) {
         auto *fn = d == 1 ? k_hs_energy_i8<1> : d == 2 ? k_hs_energy_i8<2> : d == 3 ? k_hs_energy_i8<3> : k_hs_energy_i8<4>;

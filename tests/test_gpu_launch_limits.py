@@ -23,6 +23,18 @@ def test_ising_energies_of_many_replicas():
         assert torch.equal(e[at:at + (1 << 26)], want[spins[at:at + (1 << 26)]])
 
 
+def test_hyperspin_energies_of_many_replicas():
+    """Four replicas to a block of 256 threads at D = 4."""
+    n, d, r = 2, 4, (1 << 26) + 21
+    J = torch.tensor([[0.0, 1.0], [1.0, 0.0]], device=DEV)
+    x = torch.randn((n, r, d), device=DEV)
+    e = torch.full((r,), 99.0, dtype=torch.float64, device=DEV)
+    api.chym_hs_energy(J, x, e)
+    for at in range(0, r, 1 << 25):
+        u = torch.nn.functional.normalize(x[:, at:at + (1 << 25)].double(), dim=2)
+        assert bool(((e[at:at + (1 << 25)] + 2 * (u[0] * u[1]).sum(dim=1)).abs() <= 1e-14).all())
+
+
 def test_standardize_of_many_groups():
     groups, group = (1 << 22) + 5, 2
     f = torch.rand((groups * group, 32), device=DEV)
