@@ -284,7 +284,7 @@ typedef struct chym_task {
 
 typedef struct chym_batch chym_batch; /* opaque plan (host object owned by the library) */
 
-/* Device workspace bytes a batch of these tasks (host array) needs: by the
+/* Device workspace bytes that hold a batch of these tasks (host array): by the
  * tasks alone, whatever plans are set and whichever device it runs on (no
  * device is looked at). */
 int chym_batch_workspace_size(const chym_task *tasks, int32_t n_tasks, size_t *bytes);

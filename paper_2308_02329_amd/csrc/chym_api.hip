@@ -534,9 +534,10 @@ size_t most_items(int r, int d) {
     return ((size_t)r + pack - 1) / pack;
 }
 
-// Device workspace of a batch, by its (valid) tasks alone: with the most work
-// items (one replica each for sparse rows), groups and staged couplings that a
-// plan or a device gives them.
+// Device workspace that holds a batch whatever the plans and the device, by its
+// (valid) tasks alone: with the most work items (one replica each for sparse
+// rows), groups and staged couplings that these give them.  (plan_layout's total
+// is what the present ones do.)
 size_t batch_bytes(const chym_task *tasks, int32_t n_tasks) {
     size_t items = 0, staged = 0;
     std::set<GroupKey> groups;
@@ -868,6 +869,11 @@ struct MapBatchLayout {
     size_t off_tasks, off_items, total;
 };
 
+size_t map_batch_total(const MapBatchLayout &L, size_t items) {
+    // and an unused third area: a workspace was never less than three
+    return L.off_items + align_up(sizeof(int2) * std::max<size_t>(1, items)) + kAlign;
+}
+
 // Validates the tasks, fills their kernel arguments and sizes the workspace, by
 // the tasks alone: with the most work items that a device gives them.
 int map_batch_args(const chym_map_problem *probs, const chym_run *runs, int32_t n_tasks, MapBatchLayout *L) {
@@ -890,12 +896,11 @@ int map_batch_args(const chym_map_problem *probs, const chym_run *runs, int32_t 
         if (runs[t].steps > 0) items += most_items(runs[t].r, probs[t].d);
     L->off_tasks = 0;
     L->off_items = align_up(sizeof(chym::IntegArgs) * (size_t)n_tasks);
-    // and an unused third area: a workspace was never less than three
-    L->total = L->off_items + align_up(sizeof(int2) * std::max<size_t>(1, items)) + kAlign;
+    L->total = map_batch_total(*L, items);
     return CHYM_OK;
 }
 
-// The groups and work items for the current device.
+// The groups and work items for the current device, and what they need.
 int map_batch_layout(const chym_map_problem *probs, const chym_run *runs, int32_t n_tasks, MapBatchLayout *L) {
     int rc = map_batch_args(probs, runs, n_tasks, L);
     if (rc) return rc;
@@ -924,6 +929,7 @@ int map_batch_layout(const chym_map_problem *probs, const chym_run *runs, int32_
         g.n_items = (int)L->items.size() - g.item_off;
         L->groups.push_back(g);
     }
+    L->total = map_batch_total(*L, L->items.size());
     return CHYM_OK;
 }
 
@@ -944,8 +950,7 @@ int batch_build(const chym_task *tasks, int32_t n_tasks, void *workspace, size_t
     if (rc) return rc;
     if (!workspace) return fail(CHYM_EINVAL, "workspace is NULL");
     if ((uintptr_t)workspace % kAlign) return fail(CHYM_EINVAL, "workspace must be %zu-byte aligned", kAlign);
-    const size_t need = std::max(L.total, batch_bytes(tasks, n_tasks));
-    if (ws_bytes < need) return fail(CHYM_ENOMEM, "workspace has %zu bytes, %zu needed", ws_bytes, need);
+    if (ws_bytes < L.total) return fail(CHYM_ENOMEM, "workspace has %zu bytes, %zu needed", ws_bytes, L.total);
     rc = check_device();
     if (rc) return rc;
     chym_batch *b = new (std::nothrow) chym_batch;
@@ -1386,10 +1391,10 @@ ProbeLayout probe_layout(int n, int d, int r, int steps) {
     L.off_x = L.off_pump + align_up((size_t)r * 4);
     L.off_alpha = L.off_x + align_up((size_t)n * r * d * 4);
     L.off_batch = L.off_alpha + align_up((size_t)steps * d * 4);
-    // batch workspace of one task, as batch_bytes has it; the staged couplings of
-    // a streamed-J task follow the tables (sized for three coupling terms, the
-    // most any form stages)
-    L.batch_bytes = batch_tables(1, most_items(r, d), 1).off_jf + align_up(chym::slab_jfrag_bytes((n + 15) / 16, 3));
+    // batch workspace of one task on a candidate kernel: its work list is largest
+    // with 16-replica items; the staged couplings of a streamed-J task follow the
+    // tables (sized for three coupling terms, the most any form stages)
+    L.batch_bytes = batch_tables(1, (size_t)((r + 15) / 16), 1).off_jf + align_up(chym::slab_jfrag_bytes((n + 15) / 16, 3));
     L.total = L.off_batch + L.batch_bytes;
     return L;
 }

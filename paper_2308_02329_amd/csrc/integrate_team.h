@@ -80,9 +80,8 @@ __device__ __forceinline__ float quad_norm(float x2) {
 // 2 P e s / (s^2 + A^2 e^2), which has no cancellation and needs one reciprocal.
 // For h < 0 the same with s = P + |h| and e = exp(-kl P) (P + h = A^2 / s, then
 // both sides times e^-2).  ha = |h|, kl2 = kl log2(e) with the sign of h, tiny =
-// 2^-60.  The
-// square root, reciprocal and exponential are the hardware's (each within about
-// 1 ulp).  Below s = 2^-60 the squares leave the normal floats (at h = 0 the
+// 2^-60.  The square root, reciprocal and exponential are the hardware's (each
+// within about 1 ulp).  Below s = 2^-60 the squares leave the normal floats (at h = 0 the
 // reciprocal would overflow from |A| = 4e-20 down) and the gain is 1 to within
 // 2^-60 kl.  A select rather than a branch at the end lets the rows of a lane
 // run side by side (N = 14, D = 1, 16384 replicas: 0.38 us a step, 0.60 with
@@ -344,8 +343,8 @@ constexpr int team_wpe() {
 }
 
 // One problem (items = NULL): block b integrates its replicas from
-// (first + b) * team_replicas on.  Many problems of one shape: block b integrates item b,
-// (task, replica block); the host lists the longest tasks first, and the
+// (first + b) * team_replicas on.  Many problems of one shape: block b integrates
+// item b, (task, replica block); the host lists the longest tasks first, and the
 // hardware hands the blocks out in that order.
 template <int D, int XS, int JS, int NC, int TW, bool PACK, bool MAP, int WPE = team_wpe<D, XS, JS, NC, TW, PACK>()>
 __global__ __launch_bounds__(64 * team_waves(NC, TW)) __attribute__((amdgpu_waves_per_eu(WPE)))
